@@ -647,6 +647,11 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
                      f.outs = SCH->inv(al, q);
                      return f;
                    }
+                   // Tile coordinates, whatever the interval of the branch not
+                   // taken: the range keeps the whole kernel in 32-bit indices
+                   // (64-bit ones also abort the compiler's instruction
+                   // selection on some padded-tile kernels).
+                   f.out_bound = {Mt, Nt};
                    // Full groups first, then the ragged group of r = Mt % G rows.
                    const i64 full = Mt / G * G, r = Mt % G, nfull = full * Nt;
                    Sum rest = sub(c, q, cst(nfull));
