@@ -2,6 +2,7 @@
 #include "gemm_plan.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <map>
 #include <mutex>
@@ -156,6 +157,7 @@ struct Operand {
   bool edge = false;      // some loads fall outside the operand (padded tiles)
   bool user_lds = false;  // LDS layout given by the caller
   bool direct = false;  // load vector q fills LDS slot q (direct global-to-LDS copy)
+  bool ua = false;      // vectors of 8 loaded at element alignment, cut at the operand's edges
 };
 
 }  // namespace
@@ -214,9 +216,15 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
     throw Unsupported("wave tile must be a multiple of the MFMA block and divide the workgroup tile");
   const int NWM = bm / wm, NWN = bn / wn, NWAVES = NWM * NWN, NT = 64 * NWAVES;
   if (NT > 1024) throw Unsupported("more than 16 waves per workgroup");
+  // Waves along K: each computes the whole workgroup tile (NWAVES and NT
+  // describe one of them) in LDS stages of its own.
+  const int KW = std::max(1, rq.kwaves);
+  if (KW > 1 && NWAVES != 1) throw Unsupported("waves along K need a wave tile of the workgroup tile");
   const int MI = wm / MB, NI = wn / MB, NREG = MB == 32 ? 16 : 4;
   if (MI * NI * NREG > 256) throw Unsupported("wave tile needs more than 256 accumulator registers");
-  const i64 lds_bytes = 2ll * (bm + bn) * bk * 2;
+  if (KW > 1 && ((MI * NI * NREG) % (4 * KW) || (bk / KB) % 2))
+    throw Unsupported("the waves along K do not share the accumulators evenly");
+  const i64 lds_bytes = std::max<i64>(2ll * (bm + bn) * bk * 2 * KW, KW > 1 ? 4ll * KW * bm * bn : 0);
   if (lds_bytes > 160 * 1024) throw Unsupported("two LDS stages exceed 160 KiB");
   const i64 Mt = (M + bm - 1) / bm, Nt = (N + bn - 1) / bn, Kt = (K + bk - 1) / bk, P = Mt * Nt;
 
@@ -494,6 +502,44 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
         }
       }
     }
+    // Still no 16-byte vector: rows that start at any element (an odd leading
+    // dimension) or end inside a vector.  The hardware loads 16 bytes from any
+    // element address; where the operand runs contiguously along a whole axis
+    // of at least 8 elements, vectors of 8 are loaded at element alignment
+    // and those at the operand's edges are moved inside and cut in registers.
+    // (1000 x 777 x 1001 bf16: element loads 841 us, see kernels/gemm.hip.)
+    if (o.V < 8 && tune("gemm.ua", 1)) {
+      for (int axis : {1, 0}) {
+        const i64 ext = axis == 1 ? K : o.rows_total, other = axis == 1 ? o.rows_total : K;
+        if (ext < 8 || (axis == 1 ? o.KD : o.R) % 8) continue;
+        Ctx c;
+        int x = c.var("x", ext), y = c.var("y", other);
+        SymAlg al{&c};
+        Sum row = var(c, axis == 1 ? y : x), kk = var(c, axis == 1 ? x : y);
+        // (row after row: a vector that runs past the end of a row then stays
+        // inside the operand in every k-step but the last)
+        if (key(o.is_b ? o.glob->apply(al, {kk, row}) : o.glob->apply(al, {row, kk})) !=
+            key(add(c, var(c, x), mulc(c, var(c, y), ext))))
+          continue;
+        Operand t = o;
+        t.ua = true;
+        t.axis = axis;
+        t.V = 8;
+        t.VR = t.VC = 1;
+        if (t.R * t.KD / 8 % NT) continue;
+        t.NV = (int)(t.R * t.KD / 8 / NT);
+        // the k-steps before the last are addressed by tile, k-step and thread parts
+        Ctx c2;
+        int tt = c2.var("tt", o.is_b ? Nt : Mt), kt = c2.var("kt", Kt), tid = c2.var("tid", NT), u = c2.var("u", t.NV);
+        Sum i, j;
+        load_elem(c2, t, var(c2, tid), var(c2, u), cst(0), &i, &j);
+        Sum pt, r1, pk, pl;
+        Sum off = glob_off(c2, t, var(c2, tt), var(c2, kt), i, j);
+        if (!(split_by(off, {tt}, &pt, &r1) && split_by(r1, {kt}, &pk, &pl))) continue;
+        o = t;
+        break;
+      }
+    }
     o.gaxis = o.axis;
     // An operand contiguous along m/n keeps that orientation in LDS.
     if (!o.user_lds && o.axis == 0 && o.V >= 4) o.lds = tr_lds(o.R, o.KD);
@@ -560,7 +606,7 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
   // Direct global-to-LDS copies need 16-byte global runs under the inverse
   // LDS layout and whole rounds of load vectors.
   bool direct = true;
-  direct = tune("gemm.direct", 1) != 0;
+  direct = tune("gemm.direct", 1) != 0 && !ops[0].ua && !ops[1].ua;
   if ((bk / KB) % 2) direct = false;  // the direct loop alternates fragment buffers per substep
   for (int k = 0; k < 2; ++k) {
     const Operand& o = ops[k];
@@ -612,7 +658,9 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
   }
   const i64 stage_bytes = 2ll * (bm + bn) * bk;
   int nstages = 2;
-  if (direct) {
+  if (direct && KW > 1) {
+    if (ops[0].NV + ops[1].NV > 63) throw Unsupported("the loads of a k-step exceed the load counter");
+  } else if (direct) {
     nstages = (int)std::min<i64>(4, (160 * 1024) / stage_bytes);
     // the waits count loads: NSTAGES-1 tiles behind the awaited one must fit vmcnt's 63
     const i64 per_tile = ops[0].NV + ops[1].NV;
@@ -668,6 +716,15 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
                    return f;
                  }});
   const char* pre[2] = {"a_", "b_"};
+  // Load u of the generated functions: vector u, or with vectors at element
+  // alignment element u % 8 of vector u / 8 (which of a vector's elements
+  // exist differs from one to the next).
+  auto load_var = [](Ctx& c, const Operand& o, Sum* uu, Sum* e) {
+    const int u = c.var("u", o.ua ? 8 * o.NV : o.NV);
+    *uu = o.ua ? fdiv(c, var(c, u), 8) : var(c, u);
+    *e = o.ua ? fmod(c, var(c, u), 8) : cst(0);
+    return u;
+  };
   for (int k = 0; k < 2; ++k) {
     const Operand& o = ops[k];
     std::string p = pre[k];
@@ -676,9 +733,10 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
       *tt = c.var(oo.is_b ? "tn" : "tm", oo.is_b ? Nt : Mt);
       *kt = c.var("kt", Kt);
       *tid = c.var("tid", tid_ext(oo));
-      *u = c.var("u", oo.NV);
+      Sum uu, e;
+      *u = load_var(c, oo, &uu, &e);
       Sum i, j;
-      load_elem(c, oo, var(c, *tid), var(c, *u), cst(0), &i, &j);
+      load_elem(c, oo, var(c, *tid), uu, e, &i, &j);
       return glob_off(c, oo, var(c, *tt), var(c, *kt), i, j);
     };
     if (o.sep) {
@@ -721,9 +779,11 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
     }
     fns.push_back({p + "s", [&, k](Ctx& c) {
                      const Operand& oo = ops[k];
-                     int tid = c.var("tid", tid_ext(oo)), u = c.var("u", oo.NV), e = c.var("e", oo.V);
+                     Sum uu, eu;
+                     const int tid = c.var("tid", tid_ext(oo)), u = load_var(c, oo, &uu, &eu),
+                               e = c.var("e", oo.ua ? 1 : oo.V);
                      Sum i, j;
-                     load_elem(c, oo, var(c, tid), var(c, u), var(c, e), &i, &j);
+                     load_elem(c, oo, var(c, tid), uu, oo.ua ? eu : var(c, e), &i, &j);
                      SymAlg al{&c};
                      FnSpec f;
                      f.params = {tid, u, e};
@@ -745,15 +805,75 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
                      f.outs = {oo.lds->apply(al, {row, kk})};
                      return f;
                    }});
+    if (o.ua) {
+      // Coordinates of load vector u of thread tid at tile tt and k-step kt
+      // (an expression), and the offset of its first element with the
+      // coordinates limited to the operand: along the vector to `back`
+      // elements before the extent's end, across it to the last row.
+      auto at = [&, k](Ctx& c, const Sum& kt, int* tt, int* tid, int* u, Sum* row, Sum* kk) {
+        const Operand& oo = ops[k];
+        *tt = c.var(oo.is_b ? "tn" : "tm", oo.is_b ? Nt : Mt);
+        *tid = c.var("tid", tid_ext(oo));
+        *u = c.var("u", oo.NV);
+        Sum i, j;
+        load_elem(c, oo, var(c, *tid), var(c, *u), cst(0), &i, &j);
+        *row = add(c, mulc(c, var(c, *tt), oo.R), i);
+        *kk = add(c, mulc(c, kt, oo.KD), j);
+      };
+      auto lim = [](Ctx& c, const Sum& x, i64 n, i64 to) { return select(c, lt(c, x, cst(n)), x, cst(to)); };
+      auto clamped = [&, k, at, lim](Ctx& c, bool strict) {
+        const Operand& oo = ops[k];
+        int tt, tid, u;
+        Sum row, kk;
+        at(c, cst(strict ? Kt - 1 : 0), &tt, &tid, &u, &row, &kk);
+        const i64 nr = oo.rows_total;
+        if (oo.axis == 1) {
+          row = lim(c, row, nr, nr - 1);
+          if (strict) kk = lim(c, kk, K - 8, K - 8);
+        } else if (strict) {
+          row = lim(c, row, nr - 8, nr - 8);
+          kk = lim(c, kk, K, K - 1);
+        } else {
+          row = lim(c, row, nr, nr - 8);
+        }
+        SymAlg al{&c};
+        FnSpec f;
+        f.params = {tt, tid, u};
+        f.outs = {oo.is_b ? oo.glob->apply(al, {kk, row}) : oo.glob->apply(al, {row, kk})};
+        f.out_bound = {oo.glob->phys_size()};
+        return f;
+      };
+      fns.push_back({p + "gp", [clamped](Ctx& c) { return clamped(c, false); }});
+      fns.push_back({p + "gc", [clamped](Ctx& c) { return clamped(c, true); }});
+      fns.push_back({p + "nv", [&, k, at](Ctx& c) {
+                       // elements of the vector that exist in the last k-step
+                       const Operand& oo = ops[k];
+                       int tt, tid, u;
+                       Sum row, kk;
+                       at(c, cst(Kt - 1), &tt, &tid, &u, &row, &kk);
+                       const i64 nr = oo.rows_total;
+                       const Sum x = oo.axis == 1 ? kk : row, y = oo.axis == 1 ? row : kk;
+                       const i64 nx = oo.axis == 1 ? K : nr, ny = oo.axis == 1 ? nr : K;
+                       Sum n = select(c, lt(c, x, cst(nx - 7)), cst(8),
+                                      select(c, lt(c, x, cst(nx)), sub(c, cst(nx), x), cst(0)));
+                       FnSpec f;
+                       f.params = {tt, tid, u};
+                       f.outs = {select(c, lt(c, y, cst(ny)), n, cst(0))};
+                       f.out_bound = {9};
+                       return f;
+                     }});
+    }
     if (o.edge)
       fns.push_back({p + "ok", [&, k](Ctx& c) {
                        // 1 when load vector u of thread tid at tile (tt, kt) lies
                        // inside the operand, 0 when it is padding.
                        const Operand& oo = ops[k];
                        int tt = c.var(oo.is_b ? "tn" : "tm", oo.is_b ? Nt : Mt), kt = c.var("kt", Kt),
-                           tid = c.var("tid", tid_ext(oo)), u = c.var("u", oo.NV);
+                           tid = c.var("tid", tid_ext(oo));
+                       Sum uu, e;
+                       const int u = load_var(c, oo, &uu, &e);
                        Sum i, j;
-                       load_elem(c, oo, var(c, tid), var(c, u), cst(0), &i, &j);
+                       load_elem(c, oo, var(c, tid), uu, e, &i, &j);
                        FnSpec f;
                        f.params = {tt, kt, tid, u};
                        f.outs = {in_range(c, oo, var(c, tt), var(c, kt), i, j)};
@@ -920,16 +1040,18 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
   const char* P2[2] = {"A_", "B_"};
   for (int k = 0; k < 2; ++k) {
     const Operand& o = ops[k];
-    s << "#define " << P2[k] << "NV " << o.NV << "\n#define " << P2[k] << "V " << o.V << "\n#define " << P2[k]
+    s << "#define " << P2[k] << "NV " << (o.ua ? 8 * o.NV : o.NV) << "\n#define " << P2[k] << "V " << (o.ua ? 1 : o.V) << "\n#define " << P2[k]
       << "SEP " << (o.sep ? 1 : 0) << "\n#define " << P2[k] << "SVEC " << (o.svec ? 1 : 0) << "\n#define " << P2[k]
       << "FRVEC " << (o.frvec ? 1 : 0) << "\n#define " << P2[k] << "FRTR " << (o.frtr ? 1 : 0) << "\n#define " << P2[k]
       << "FRDW " << (o.frdw ? 1 : 0) << "\n#define " << P2[k] << "FRDW_D " << o.frdw_d << "\n#define " << P2[k]
       << "FRZP " << (o.frzp ? 1 : 0) << "\n#define " << P2[k]
-      << "NVEC " << o.NVEC << "u\n#define " << P2[k]
+      << "NVEC " << (o.ua ? 8 * o.NVEC : o.NVEC) << "u\n#define " << P2[k]
       << "GUARD " << (o.guard ? 1 : 0) << "\n#define " << P2[k] << "EDGE " << (o.edge ? 1 : 0) << "\n#define "
+      << P2[k] << "UA " << (o.ua ? 1 : 0) << "\n#define " << P2[k] << "LOC_T "
+      << (!o.ua ? "IDX_T" : (2 * o.glob->phys_size() < (i64(1) << 31) ? "int" : "i64")) << "\n#define "
       << P2[k] << "BUF " << (o.direct && 2 * o.glob->phys_size() < (i64(1) << 31) ? 1 : 0) << "\n#define "
       << P2[k] << "BYTES " << 2 * o.glob->phys_size() << "u\n#define " << P2[k] << "VR " << o.VR << "\n#define "
-      << P2[k] << "VC " << (o.axis == 2 ? o.VC : o.V) << "\n";
+      << P2[k] << "VC " << (o.axis == 2 ? o.VC : o.ua ? 1 : o.V) << "\n";
     // Block vectors: element index of block position (r, c), row-major.
     s << "static constexpr int " << P2[k] << "BIDX[] = {";
     if (o.axis == 2) {
@@ -946,7 +1068,7 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
     }
     s << "};\n";
   }
-  s << "#define C_EDGE " << (cedge ? 1 : 0) << "\n";
+  s << "#define C_EDGE " << (cedge ? 1 : 0) << "\n#define KWAVES " << KW << "\n";
   // Two staging register sets when the accumulators live in AGPRs (one wave
   // per SIMD leaves the VGPRs for them); one otherwise, so two waves fit.
   int prefetch = (MI * NI * NREG > 128) ? 2 : 1;
@@ -990,7 +1112,9 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
   // Not with padded tiles: the range checks of two tiles' copies do not fit
   // the registers beside the walk's state (8000^3 bf16: 240 VGPRs spilled
   // with 8 waves, 613 with 4; none without the walk).
-  const bool persist = direct && Kt >= nstages && !(ops[0].edge || ops[1].edge || cedge) &&
+  // Waves along K keep no state of the next tile, padded or not.
+  const bool persist = direct &&
+                       (KW > 1 || (Kt >= nstages && !(ops[0].edge || ops[1].edge || cedge))) &&
                        tune("gemm.persist", 1) != 0;
   s << "#define C_SEP " << (csep ? 1 : 0) << "\n#define PERSIST " << (persist ? 1 : 0) << "\n" << code << "// ---- template ----\n" << tpl_gemm;
 
@@ -998,31 +1122,118 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
   g.src = s.str();
   g.kernel = "lego_gemm";
   g.grid = P;
-  g.block = NT;
+  g.block = NT * KW;
   g.persistent = persist;
   std::ostringstream info;
   info << "gemm " << M << "x" << N << "x" << K << (rq.dtype == LEGO_BF16 ? " bf16" : " f16") << " tile " << bm << "x"
-       << bn << "x" << bk << " waves " << NWM << "x" << NWN << " wave " << wm << "x" << wn << " mfma " << MB << "x"
-       << MB << "x" << KB << " sched" << (xcd ? "+xcd" : "") << " A:V" << ops[0].V
+       << bn << "x" << bk << " waves " << NWM << "x" << NWN << (KW > 1 ? "x" + std::to_string(KW) + "k" : "") << " wave " << wm << "x" << wn << " mfma " << MB << "x"
+       << MB << "x" << KB << " sched" << (xcd ? "+xcd" : "") << " A:V" << ops[0].V << (ops[0].ua ? "u" : "")
        << (ops[0].gaxis == 2 ? "b" + std::to_string(ops[0].VR) + "x" + std::to_string(ops[0].VC) : (ops[0].gaxis ? "k" : "m"))
        << (ops[0].sep ? " sep" : " full") << (ops[0].svec ? " svec" : " sscalar")
-       << (ops[0].frvec ? " frvec" : (ops[0].frtr ? " frtr" : (ops[0].frzp ? " frzpair" : (ops[0].frdw ? " frdw" : " frscalar")))) << " B:V" << ops[1].V
+       << (ops[0].frvec ? " frvec" : (ops[0].frtr ? " frtr" : (ops[0].frzp ? " frzpair" : (ops[0].frdw ? " frdw" : " frscalar")))) << " B:V" << ops[1].V << (ops[1].ua ? "u" : "")
        << (ops[1].gaxis == 2 ? "b" + std::to_string(ops[1].VR) + "x" + std::to_string(ops[1].VC) : (ops[1].gaxis ? "k" : "n"))
        << (ops[1].sep ? " sep" : " full") << (ops[1].svec ? " svec" : " sscalar")
        << (ops[1].frvec ? " frvec" : (ops[1].frtr ? " frtr" : (ops[1].frdw ? " frdw" : " frscalar"))) << (csep ? " C:sep" : " C:full") << (wide ? " i64" : " u32")
        << (direct ? " direct-lds" : " staged")
        << (direct ? std::string(dma_spread ? " spread" : " burst") + " fd" + std::to_string(frag_dist) : "")
        << (ragged_groups ? " ragged-groups" : "")
-       << (ops[0].edge || ops[1].edge || cedge ? " edges" : "") << (persist ? " persistent" : "") << " stages " << nstages << " lds " << nstages * stage_bytes
+       << (ops[0].edge || ops[1].edge || cedge ? " edges" : "") << (persist ? " persistent" : "") << " stages " << nstages << " lds " << (KW > 1 ? lds_bytes : nstages * stage_bytes)
        << "B ops" << opsinfo.str();
   g.info = info.str();
+  g.direct = direct;
+  g.vec8 = ops[0].V == 8 && ops[1].V == 8;
   g.wide_ok = direct && !((ops[0].frtr || ops[1].frtr) && (ops[0].edge || ops[1].edge || cedge));
   return g;
 }
 
 }  // namespace
 
-GemmPlan plan_gemm(const GemmRequest& rq) {
+namespace {
+
+// A workgroup tile of the default plans.  The time of a GEMM with it is taken
+// as rounds * k-steps * step + fixed, rounds = ceil(tiles / 256 CUs), a 64-deep
+// k-step costing `step` with few tiles and `step + full` when every CU has one
+// (L2 and power are shared), in microseconds.  Fitted to graph-replayed
+// launches of 22 shapes (fp16; in brackets the tile that is now taken and the
+// 256-wide tile that was the only default):
+//   2048^3 row/row 25.3 (128) / 41.0, 1024^3 7.4 (64) / 22.5, 512^3 3.4 (32) /
+//   14.2, 960x576x832 6.5 (64) / 18.5, 256x3712x1024 7.3 (64) / 21.8,
+//   128x8192x8192 44.4 (64) / 108, 256x256x8192 13.0 (32) / 120,
+//   1536x1536x4096 31.7 (128) / 68.5, 3999x2001x1111 36.7 (128) / 48.1;
+//   256-wide tiles stay ahead at 3000^3 (84 against 106 with 128) and
+//   1344x5696x5952 (117 against 133).
+// The 64- and 32-wide tiles are computed whole by each of 4 waves along K:
+// without barriers and with half the LDS reads they measured 7.4 against 7.6
+// (1024^3), 7.3 against 8.7 (256x3712x1024) and 22.3 against 28.9 us
+// (256x256x8192) of 4 waves with 32x32 of the tile each.
+struct TileChoice {
+  int b, wm, wn, kwaves;
+  double step, full, fixed;
+};
+const TileChoice kTiles[] = {
+    {256, 0, 0, 0, 1.15, 0.6, 6.0},  // wave tiles by the rule of plan_gemm
+    {128, 64, 32, 0, 0.43, 0.25, 4.0},
+    {64, 64, 64, 4, 0.15, 0.13, 3.0},
+    {32, 32, 32, 4, 0.08, 0.04, 2.5},
+};
+
+const TileChoice& choose_tile(const GemmRequest& rq) {
+  const TileChoice* best = nullptr;
+  double best_t = 0;
+  for (const TileChoice& t : kTiles) {
+    const double p = (double)((rq.M + t.b - 1) / t.b) * (double)((rq.N + t.b - 1) / t.b);
+    const double fill = std::min(1.0, p / 256), steps = (double)((rq.K + 63) / 64);
+    const double full = t.full * (t.b == 256 ? fill * fill : fill);
+    const double us = std::ceil(p / 256) * steps * (t.step + full) + t.fixed;
+    if (!best || us < best_t) best = &t, best_t = us;
+  }
+  return *best;
+}
+
+}  // namespace
+
+GemmPlan plan_gemm(const GemmRequest& rq0) {
+  GemmRequest rq = rq0;
+  // The tile is the planner's to choose when the descriptor gives none of it,
+  // nor a layout or a stage count that was made for the 256-wide default.
+  const bool free_tile = !rq.bm && !rq.bn && !rq.bk && !rq.wm && !rq.wn && !rq.sched && !rq.lds_a && !rq.lds_b &&
+                         !rq.stages && rq.M > 0 && rq.N > 0 && rq.K > 0;
+  if (free_tile && tune("gemm.bm", 0)) {
+    rq.bm = (int)tune("gemm.bm", 0), rq.bn = (int)tune("gemm.bn", 0), rq.bk = (int)tune("gemm.bk", 64);
+    rq.wm = (int)tune("gemm.wm", 0), rq.wn = (int)tune("gemm.wn", 0);
+    rq.kwaves = (int)tune("gemm.kwaves", 0);
+    rq.stages = (int)tune("gemm.stages", 0);
+  } else if (free_tile) {
+    const TileChoice& t = choose_tile(rq);
+    if (t.b < 256) {
+      rq.bm = rq.bn = t.b;
+      rq.wm = t.wm, rq.wn = t.wn;
+      rq.kwaves = t.kwaves;
+      rq.bk = 64;
+      if (!t.kwaves) return plan_gemm_waves(rq, true);
+      // 64-wide tiles along K: 32-deep steps spread a short K over the waves
+      // more evenly (960x576x832: 6.5 against 7.2 us, 1000x777x1001 with odd
+      // rows 10.8 against 15.2; 128x8192x8192 the other way, 58.7 against
+      // 44.4), and staged loads of 64 leave too few registers.
+      // (The 16x16x32 instruction has one substep in 32, which the waves
+      // along K cannot halve.)
+      GemmPlan p = plan_gemm_waves(rq, true);
+      if (!p.vec8) {
+        // Loads narrower than 16 bytes take more registers than a wave along
+        // K has: 4 waves with 32x32 of a 64x64 tile each.
+        rq.bm = rq.bn = 64, rq.wm = rq.wn = 32, rq.kwaves = 0;
+        return plan_gemm_waves(rq, true);
+      }
+      if (t.b == 64 && (rq.K <= 1024 || !p.direct)) {
+        try {
+          rq.bk = 32;
+          return plan_gemm_waves(rq, true);
+        } catch (const Unsupported&) {
+        }
+      }
+      return p;
+    }
+  }
   // 128x128 wave tiles (4 waves) win where the copies are direct: 0.852
   // against 0.876 ms for 8 waves of 128x64 on the 8192^3 bf16 GEMM, reading
   // 1/3 less LDS per MFMA, and 1-5% with transposing fragment reads (8192^3

@@ -19,6 +19,7 @@ struct GemmRequest {
   int dtype = LEGO_BF16;
   int bm = 0, bn = 0, bk = 0, wm = 0, wn = 0, group_m = 0, xcd = 0;
   int stages = 0;  // LDS stages; 0: chosen
+  int kwaves = 0;  // chosen by the planner: waves that share a workgroup tile along K (<= 1: none)
   LayoutP a, b, c, sched, lds_a, lds_b;  // null: defaults
   LayoutP frag_a, frag_b, frag_c;        // null: chosen; else they select the MFMA instruction
 };
@@ -27,6 +28,8 @@ struct GemmPlan : KernelPlan {
   // direct global-to-LDS copies whose 128x128 wave tiles fit the registers
   // (not transposing reads with padded tiles)
   bool wide_ok = false;
+  bool direct = false;  // global-to-LDS copies without registers
+  bool vec8 = false;    // both operands are loaded 16 bytes at a time
 };
 
 GemmRequest gemm_request(const lego_gemm_desc& d, const std::function<LayoutP(lego_layout_t)>& resolve);

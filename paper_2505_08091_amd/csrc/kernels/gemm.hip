@@ -45,13 +45,41 @@
 //       operand (Section III-D partial tiles): load vector u is inside (1) or
 //       padding (0, read as zero); the operand's size in bytes
 //   C_EDGE, c_ok(tm, tn, lane, w, mi, ni, r): the C element exists
+//   A_UA (and B_*): the operand's rows are not aligned to its load vectors or
+//       its extents not multiples of them: A_NV, A_V, a_gl, a_s and a_ok
+//       describe single elements, u = 8 * vector + element; the vectors of 8
+//       are loaded at element alignment, a_gp(tm, tid, u) being the offset of load vector u of the
+//       tile's first k-step with vectors past the operand's rows moved onto
+//       it, and, for the last k-step, a_gc(tm, tid, u) the offset moved back
+//       until all 8 elements lie inside the operand and a_nv(tm, tid, u) how
+//       many of the vector's elements exist (0..8); A_LOC_T is a signed type
+//       that holds offsets inside a tile
+//   KWAVES           > 1: each of KWAVES waves computes the whole workgroup tile
+//                    over every KWAVES-th k-step in LDS stages of its own (the
+//                    generated functions describe one wave, NT = 64), and the
+//                    partial sums are added through LDS
 //   A_VR A_VC A_BIDX (and B_*): a load vector that is an A_VR x A_VC block of
 //       the tile; A_BIDX[r * A_VC + c] is the vector element at block (r, c),
 //       and each block row is stored to LDS as one A_VC-element vector
 
 typedef unsigned short elem_t;
-typedef elem_t av_t __attribute__((ext_vector_type(A_V)));
-typedef elem_t bv_t __attribute__((ext_vector_type(B_V)));
+// Load vectors per thread and their width.
+#if A_UA
+#define A_NL (A_NV / 8)
+#define A_W 8
+#else
+#define A_NL A_NV
+#define A_W A_V
+#endif
+#if B_UA
+#define B_NL (B_NV / 8)
+#define B_W 8
+#else
+#define B_NL B_NV
+#define B_W B_V
+#endif
+typedef elem_t av_t __attribute__((ext_vector_type(A_W)));
+typedef elem_t bv_t __attribute__((ext_vector_type(B_W)));
 typedef elem_t e8_t __attribute__((ext_vector_type(8)));
 #if IN_BF16
 typedef __bf16 mf_t __attribute__((ext_vector_type(8)));
@@ -160,7 +188,9 @@ LEGO_FN mf_t lds_frag_tr(const elem_t* base, IDX_T off0, IDX_T off1) {
 #ifndef DMA_ROWS
 #define DMA_ROWS (FRAG_DIST * MFMA_ROWS)
 #endif
-#if (BK / KB) % (FRAG_DIST + 1) == 0
+#if KWAVES > 1
+#define NFB (2 * (BK / KB))  // the fragments of two k-steps
+#elif (BK / KB) % (FRAG_DIST + 1) == 0
 #define NFB (FRAG_DIST + 1)
 #else
 #define NFB (BK / KB)
@@ -179,10 +209,53 @@ struct lego_bool {
   static constexpr bool value = B;
 };
 
-extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restrict__ A, const elem_t* __restrict__ B,
-                                                           float* __restrict__ C) {
-  __shared__ __attribute__((aligned(16))) elem_t lds[NSTAGES * STAGE];
+#define UA_ANY (A_UA || B_UA)
+#if UA_ANY
+// Rows of odd length, or that start at any element: loading such an operand
+// element by element bound the kernel by load instructions (1000x777x1001
+// bf16: 841 us with 256-wide tiles).  The hardware loads 16 bytes from any
+// element address, at up to two cache lines per row segment: 27.5 us with the
+// same tiles, 9.5 us with the 64-wide ones that fill the chip; 4001^3 fp16
+// 165 us (0.78 PFLOP/s).
+// 8 elements at element alignment, and the first n of them (the rest zero) of
+// a vector that was loaded 8 - n elements early.
+typedef e8_t e8u_t __attribute__((aligned(2)));
+LEGO_FN e8_t ua_load(const elem_t* p) { return *(const e8u_t*)p; }
+LEGO_FN e8_t ua_first(e8_t v, IDX_T n) {
+  typedef u64 u64x2 __attribute__((ext_vector_type(2)));
+  u64x2 x = __builtin_bit_cast(u64x2, v);
+  const unsigned sh = 128u - 16u * (unsigned)n;  // bits to drop: 0 for n = 8
+  if (sh >= 64u) {
+    x[0] = sh < 128u ? x[1] >> (sh - 64u) : 0;
+    x[1] = 0;
+  } else if (sh > 0u) {
+    x[0] = (x[0] >> sh) | (x[1] << (64u - sh));
+    x[1] >>= sh;
+  }
+  return __builtin_bit_cast(e8_t, x);
+}
+#endif
+
+#if KWAVES > 1
+#define BLOCK (64 * KWAVES)
+// The partial sums of all waves (MI * NI * NREG floats a lane) reuse the stages.
+#define RED_ELEMS (KWAVES * MI * NI * NREG * 64 * 2)
+#define LDS_ELEMS (KWAVES * NSTAGES * STAGE > RED_ELEMS ? KWAVES * NSTAGES * STAGE : RED_ELEMS)
+#else
+#define BLOCK NT
+#define LDS_ELEMS (NSTAGES * STAGE)
+#endif
+extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __restrict__ A,
+                                                              const elem_t* __restrict__ B, float* __restrict__ C) {
+#if KWAVES > 1
+  __shared__ __attribute__((aligned(16))) elem_t lds_all[LDS_ELEMS];
+  const IDX_T tid = threadIdx.x % 64u;
+  const IDX_T kw = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);  // this wave's part of K
+  elem_t* const lds = lds_all + kw * (NSTAGES * STAGE);
+#else
+  __shared__ __attribute__((aligned(16))) elem_t lds[LDS_ELEMS];
   const IDX_T tid = threadIdx.x;
+#endif
   const IDX_T lane = tid % 64u;
   const IDX_T w = tid / 64u;
   IDX_T tm, tn;
@@ -190,15 +263,27 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
 
 #if A_SEP
   const elem_t* __restrict__ Ab = A + a_gt(tm);
-  IDX_T a_loc[A_NV];
+  A_LOC_T a_loc[A_NL];
 #pragma unroll
-  for (int u = 0; u < A_NV; ++u) a_loc[u] = a_gl(tid, u);
+  for (int u = 0; u < A_NL; ++u) {
+#if A_UA
+    a_loc[u] = (A_LOC_T)a_gp(tm, tid, u) - (A_LOC_T)a_gt(tm);
+#else
+    a_loc[u] = a_gl(tid, u);
+#endif
+  }
 #endif
 #if B_SEP
   const elem_t* __restrict__ Bb = B + b_gt(tn);
-  IDX_T b_loc[B_NV];
+  B_LOC_T b_loc[B_NL];
 #pragma unroll
-  for (int u = 0; u < B_NV; ++u) b_loc[u] = b_gl(tid, u);
+  for (int u = 0; u < B_NL; ++u) {
+#if B_UA
+    b_loc[u] = (B_LOC_T)b_gp(tn, tid, u) - (B_LOC_T)b_gt(tn);
+#else
+    b_loc[u] = b_gl(tid, u);
+#endif
+  }
 #endif
 
   // Global-to-LDS staging registers.  With PREFETCH == 2 there are two sets:
@@ -210,8 +295,8 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
 #else
 #define NSETS PREFETCH
 #endif
-  av_t ra[NSETS][A_NV];
-  bv_t rb[NSETS][B_NV];
+  av_t ra[NSETS][A_NL];
+  bv_t rb[NSETS][B_NL];
   acc_t acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -255,49 +340,66 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
         }
   };
 
-  // Load vectors [lo, hi) of the tile for step kt (A's A_NV vectors, then
-  // B's B_NV) into staging set rbuf.
-  auto gload_part = [&](IDX_T kt, int rbuf, int lo, int hi) {
+  // Load vectors [lo, hi) of the tile for step kt (A's A_NL vectors, then
+  // B's B_NL) into staging set rbuf.
+  // The sums run over the k-steps in any order.  With vectors at element
+  // alignment the last k-step, whose vectors are moved and cut, comes first:
+  // it is loaded and stored ahead of the loop (`first`, known at compile
+  // time), and the loop carries no such code.
+  auto gload_part = [&](IDX_T t, int rbuf, int lo, int hi, auto first_t) {
+    constexpr bool first = decltype(first_t)::value;
+    const IDX_T kt = !UA_ANY ? t : first ? (IDX_T)(KT - 1) : t - 1;
 #pragma unroll
-    for (int u = 0; u < A_NV; ++u) {
+    for (int u = 0; u < A_NL; ++u) {
       if (u < lo || u >= hi) continue;
       if (A_GUARD && (IDX_T)u * NT + tid >= A_NVEC) continue;
-#if A_EDGE
+#if A_UA
+      ra[rbuf][u] = first ? ua_load(A + a_gc(tm, tid, u)) : ua_load(Ab + a_gk(kt) + a_loc[u]);
+      continue;
+#elif A_EDGE
       if (!a_ok(tm, kt, tid, u)) {
         ra[rbuf][u] = (av_t){};
         continue;
       }
 #endif
-#if A_SEP
+#if A_UA
+#elif A_SEP
       ra[rbuf][u] = *(const av_t*)(Ab + a_gk(kt) + a_loc[u]);
 #else
       ra[rbuf][u] = *(const av_t*)(A + a_gf(tm, kt, tid, u));
 #endif
     }
 #pragma unroll
-    for (int u = 0; u < B_NV; ++u) {
-      if (A_NV + u < lo || A_NV + u >= hi) continue;
+    for (int u = 0; u < B_NL; ++u) {
+      if (A_NL + u < lo || A_NL + u >= hi) continue;
       if (B_GUARD && (IDX_T)u * NT + tid >= B_NVEC) continue;
-#if B_EDGE
+#if B_UA
+      rb[rbuf][u] = first ? ua_load(B + b_gc(tn, tid, u)) : ua_load(Bb + b_gk(kt) + b_loc[u]);
+      continue;
+#elif B_EDGE
       if (!b_ok(tn, kt, tid, u)) {
         rb[rbuf][u] = (bv_t){};
         continue;
       }
 #endif
-#if B_SEP
+#if B_UA
+#elif B_SEP
       rb[rbuf][u] = *(const bv_t*)(Bb + b_gk(kt) + b_loc[u]);
 #else
       rb[rbuf][u] = *(const bv_t*)(B + b_gf(tn, kt, tid, u));
 #endif
     }
   };
-  auto gload = [&](IDX_T kt, int rbuf) { gload_part(kt, rbuf, 0, A_NV + B_NV); };
+  auto gload = [&](IDX_T t, int rbuf) { gload_part(t, rbuf, 0, A_NL + B_NL, lego_bool<false>()); };
+  auto gload_first = [&]() { gload_part(0, 0, 0, A_NL + B_NL, lego_bool<UA_ANY>()); };
   // Write vectors [lo, hi) of staging set rbuf to LDS stage `stage`.
-  auto sstore_part = [&](int stage, int rbuf, int lo, int hi) {
+  auto sstore_part = [&](int stage, int rbuf, int lo, int hi, auto first_t) {
+    constexpr bool first = decltype(first_t)::value;
+    (void)first;
     elem_t* la = lds + stage * STAGE;
     elem_t* lb = la + A_STAGE;
 #pragma unroll
-    for (int u = 0; u < A_NV; ++u) {
+    for (int u = 0; u < A_NL; ++u) {
       if (u < lo || u >= hi) continue;
       if (A_GUARD && (IDX_T)u * NT + tid >= A_NVEC) continue;
 #if A_VR > 1 && A_SVEC
@@ -309,16 +411,23 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
         for (int c = 0; c < A_VC; ++c) piece[c] = ra[rbuf][u][A_BIDX[r * A_VC + c]];
         *(ar_t*)(la + a_s(tid, u, A_BIDX[r * A_VC])) = piece;
       }
-#elif A_SVEC
-      *(av_t*)(la + a_s(tid, u, 0)) = ra[rbuf][u];
+#else
+#if A_UA
+      const av_t va = first ? ua_first(ra[rbuf][u], a_nv(tm, tid, u)) : ra[rbuf][u];
+#else
+      const av_t va = ra[rbuf][u];
+#endif
+#if A_SVEC
+      *(av_t*)(la + a_s(tid, A_UA ? 8 * u : u, 0)) = va;
 #else
 #pragma unroll
-      for (int e = 0; e < A_V; ++e) la[a_s(tid, u, e)] = ra[rbuf][u][e];
+      for (int e = 0; e < A_W; ++e) la[A_UA ? a_s(tid, 8 * u + e, 0) : a_s(tid, u, e)] = va[e];
+#endif
 #endif
     }
 #pragma unroll
-    for (int u = 0; u < B_NV; ++u) {
-      if (A_NV + u < lo || A_NV + u >= hi) continue;
+    for (int u = 0; u < B_NL; ++u) {
+      if (A_NL + u < lo || A_NL + u >= hi) continue;
       if (B_GUARD && (IDX_T)u * NT + tid >= B_NVEC) continue;
 #if B_VR > 1 && B_SVEC
       typedef elem_t br_t __attribute__((ext_vector_type(B_VC)));
@@ -329,16 +438,24 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
         for (int c = 0; c < B_VC; ++c) piece[c] = rb[rbuf][u][B_BIDX[r * B_VC + c]];
         *(br_t*)(lb + b_s(tid, u, B_BIDX[r * B_VC])) = piece;
       }
-#elif B_SVEC
-      *(bv_t*)(lb + b_s(tid, u, 0)) = rb[rbuf][u];
+#else
+#if B_UA
+      const bv_t vb = first ? ua_first(rb[rbuf][u], b_nv(tn, tid, u)) : rb[rbuf][u];
+#else
+      const bv_t vb = rb[rbuf][u];
+#endif
+#if B_SVEC
+      *(bv_t*)(lb + b_s(tid, B_UA ? 8 * u : u, 0)) = vb;
 #else
 #pragma unroll
-      for (int e = 0; e < B_V; ++e) lb[b_s(tid, u, e)] = rb[rbuf][u][e];
+      for (int e = 0; e < B_W; ++e) lb[B_UA ? b_s(tid, 8 * u + e, 0) : b_s(tid, u, e)] = vb[e];
+#endif
 #endif
     }
   };
 
-  auto sstore = [&](int stage, int rbuf) { sstore_part(stage, rbuf, 0, A_NV + B_NV); };
+  auto sstore = [&](int stage, int rbuf) { sstore_part(stage, rbuf, 0, A_NL + B_NL, lego_bool<false>()); };
+  auto sstore_first = [&]() { sstore_part(0, 0, 0, A_NL + B_NL, lego_bool<UA_ANY>()); };
 
   // Fragments of one k-substep, double-buffered in registers: the reads of
   // substep s+1 are in flight while the MFMAs of substep s run.
@@ -456,7 +573,7 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
       if (s == STORE_AT) {
         // Spread the LDS stores between the MFMAs of this substep.
 #pragma unroll
-        for (int g = 0; g < A_NV * (A_SVEC ? A_VR : A_V) + B_NV * (B_SVEC ? B_VR : B_V); ++g) {
+        for (int g = 0; g < A_NL * (A_SVEC ? A_VR : A_V) + B_NL * (B_SVEC ? B_VR : B_V); ++g) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
           __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // one LDS write
         }
@@ -481,7 +598,11 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
   // dispatched to).  The ring runs on across tile boundaries: the last steps
   // of one tile request the first steps of the next, so the C stores of a
   // tile are issued while the next tile's operands are already on the way.
+#if KWAVES > 1
+  const IDX_T wu = 0;
+#else
   const IDX_T wu = __builtin_amdgcn_readfirstlane(tid / 64u);
+#endif
 #if A_BUF || B_BUF
   // Range-checked buffer loads: an offset past the buffer's end (0xFFFFFFFF
   // for padding) writes zero to the LDS slot instead of reading memory.
@@ -509,12 +630,42 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
 #endif
     return t;
   };
-  // Copies [lo, hi) of step kt of tile t (A's A_NV vectors, then B's).
-  auto dload_part = [&](const Tile& t, IDX_T kt, int stage, int lo, int hi) {
+  // Padded tiles: a copy past the operand's rows passes an offset beyond any
+  // buffer (whatever the scalar part, which stays below 2^31), set once per
+  // tile.  Only the last k-step also ends inside K: the k-steps run in the
+  // order KT - 1, 0, 1, ... and its copies, which test every vector, go out
+  // ahead of the loop (`first`, known at compile time).  (Tested at every
+  // copy, the offsets of all steps filled the registers: up to 39 spilled in
+  // the 64-wide plans of waves along K, none now.)
+  constexpr bool EDGE_K = (A_EDGE || B_EDGE) && GEMM_K % BK != 0;
+  constexpr unsigned OUTSIDE = 0x80000000u;
+#if A_EDGE && A_SEP
+  unsigned a_vo[A_NL];
+#endif
+#if B_EDGE && B_SEP
+  unsigned b_vo[B_NL];
+#endif
+  auto set_edges = [&](const Tile& t) {
+    (void)t;
+#if A_EDGE && A_SEP
+#pragma unroll
+    for (int u = 0; u < A_NL; ++u) a_vo[u] = a_ok(t.tm, 0, tid, u) ? (unsigned)a_loc[u] * 2u : OUTSIDE;
+#endif
+#if B_EDGE && B_SEP
+#pragma unroll
+    for (int u = 0; u < B_NL; ++u) b_vo[u] = b_ok(t.tn, 0, tid, u) ? (unsigned)b_loc[u] * 2u : OUTSIDE;
+#endif
+  };
+  // Copies [lo, hi) of the step-th k-step of tile t (A's A_NL vectors, then B's).
+  auto dload_part = [&](const Tile& t, IDX_T step, int stage, int lo, int hi, auto first_t) {
+    constexpr bool first = decltype(first_t)::value;
+    (void)first;
+    // (later requests of step 0 land in stages nothing reads: k-step 0 again)
+    const IDX_T kt = !EDGE_K ? step : step != 0 ? step - 1 : first ? (IDX_T)(KT - 1) : 0;
     elem_t* la = lds + stage * STAGE;
     elem_t* lb = la + A_STAGE;
 #pragma unroll
-    for (int u = 0; u < A_NV; ++u) {
+    for (int u = 0; u < A_NL; ++u) {
       if (u < lo || u >= hi) continue;
 #if A_SEP
       const elem_t* src = t.ab + a_gk(kt) + a_loc[u];
@@ -523,7 +674,12 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
 #endif
       __attribute__((address_space(3))) void* dst = (__attribute__((address_space(3))) void*)(la + ((IDX_T)u * NT + wu * 64u) * 8u);
 #if A_BUF
-#if A_EDGE
+#if A_EDGE && A_SEP
+      (void)src;
+      const unsigned soff = (unsigned)((t.ab - A) + a_gk(kt)) * 2u;
+      const unsigned off = !first ? a_vo[u] : a_ok(t.tm, kt, tid, u) ? (unsigned)a_loc[u] * 2u : OUTSIDE;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, dst, 16, off, soff, 0, 0);
+#elif A_EDGE
       const unsigned off = a_ok(t.tm, kt, tid, u) ? (unsigned)((src - A) * 2) : 0xFFFFFFFFu;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, dst, 16, off, 0, 0, 0);
 #elif A_SEP
@@ -540,8 +696,8 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
 #endif
     }
 #pragma unroll
-    for (int u = 0; u < B_NV; ++u) {
-      if (A_NV + u < lo || A_NV + u >= hi) continue;
+    for (int u = 0; u < B_NL; ++u) {
+      if (A_NL + u < lo || A_NL + u >= hi) continue;
 #if B_SEP
       const elem_t* src = t.bb + b_gk(kt) + b_loc[u];
 #else
@@ -549,7 +705,12 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
 #endif
       __attribute__((address_space(3))) void* dst = (__attribute__((address_space(3))) void*)(lb + ((IDX_T)u * NT + wu * 64u) * 8u);
 #if B_BUF
-#if B_EDGE
+#if B_EDGE && B_SEP
+      (void)src;
+      const unsigned soff = (unsigned)((t.bb - B) + b_gk(kt)) * 2u;
+      const unsigned off = !first ? b_vo[u] : b_ok(t.tn, kt, tid, u) ? (unsigned)b_loc[u] * 2u : OUTSIDE;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, off, soff, 0, 0);
+#elif B_EDGE
       const unsigned off = b_ok(t.tn, kt, tid, u) ? (unsigned)((src - B) * 2) : 0xFFFFFFFFu;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, off, 0, 0, 0);
 #elif B_SEP
@@ -567,27 +728,173 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
   // s_waitcnt with only vmcnt constrained (expcnt and lgkmcnt at their maxima).
 #define VMCNT_WAIT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | ((((n) >> 4) & 3) << 14) | 0x70 | 0xF00)
   // Wait until at most `after` tiles of direct loads are still in flight.
-  static_assert((NSTAGES - 1) * (A_NV + B_NV) <= 63, "vmcnt counts at most 63 loads");
+  static_assert((NSTAGES - 1) * (A_NL + B_NL) <= 63, "vmcnt counts at most 63 loads");
   auto wait_tiles = [&](int after) {
     if (after <= 0) VMCNT_WAIT(0);
-    else if (after == 1) VMCNT_WAIT(1 * (A_NV + B_NV));
+    else if (after == 1) VMCNT_WAIT(1 * (A_NL + B_NL));
 #if NSTAGES > 2
-    else if (after == 2) VMCNT_WAIT(2 * (A_NV + B_NV));
+    else if (after == 2) VMCNT_WAIT(2 * (A_NL + B_NL));
 #endif
 #if NSTAGES > 3
-    else VMCNT_WAIT(3 * (A_NV + B_NV));  // (waits longer than needed beyond 3)
+    else VMCNT_WAIT(3 * (A_NL + B_NL));  // (waits longer than needed beyond 3)
 #endif
   };
+#endif  // DIRECT_LDS
+#if KWAVES > 1
+  // Each wave computes the workgroup's whole tile over the k-steps kw,
+  // kw + KWAVES, ...: no two waves share LDS data, so a wave waits for its own
+  // loads only and the k-loop has no barrier, and a wave tile as large as the
+  // workgroup tile reads each operand fragment once.  The waves' partial sums
+  // meet in LDS at the end of a tile, each wave adding and storing its share
+  // of the accumulator registers of all.  Bound by the copies' path into LDS
+  // (64 bytes a clock and CU: 256 clocks for a 64x64x64 step, of which the
+  // MFMAs take 128) and, for short K, by the first copies' latency.  Graph
+  // replays, fp16, against 4 waves with a quarter of the tile each and a
+  // barrier per step: 1024^3 7.6 -> 7.4 us, 256x3712x1024 8.7 -> 7.3,
+  // 256x256x8192 28.9 -> 22.3 (13.0 with 32-wide tiles), 512^3 4.6 -> 3.4
+  // with 32-wide tiles.
+  constexpr int S = BK / KB;
+  constexpr int NACC = MI * NI * NREG;  // accumulators a lane
+  constexpr int GPW = NACC / 4 / KWAVES;  // groups of 4 a wave adds
+  typedef float f4_t __attribute__((ext_vector_type(4)));
+  // Orders this wave's LDS writes and reads (other lanes read what a lane
+  // wrote); the LDS serves one wave's operations in issue order.
+#define WAVE_FENCE()                                       \
+  do {                                                     \
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); \
+    __builtin_amdgcn_wave_barrier();                       \
+  } while (0)
+  IDX_T pid = blockIdx.x;
+  // (at least one tile a workgroup: the grid is never larger than the tiles)
+  do {
+    const IDX_T n = (IDX_T)KT > kw ? ((IDX_T)KT - kw + KWAVES - 1) / KWAVES : 0;  // this wave's k-steps
+#if DIRECT_LDS
+    const Tile cur = tile_of(pid);
+    tm = cur.tm;
+    tn = cur.tn;
+    set_edges(cur);
+    if (EDGE_K && kw == 0)
+      dload_part(cur, kw, 0, 0, A_NL + B_NL, lego_bool<true>());
+    else if (n > 0)
+      dload_part(cur, kw, 0, 0, A_NL + B_NL, lego_bool<false>());
+    if (n > 1) dload_part(cur, kw + KWAVES, 1, 0, A_NL + B_NL, lego_bool<false>());
+    if (n > 0) {
+      wait_tiles(n > 1 ? 1 : 0);
+      __builtin_amdgcn_sched_barrier(0);
+      WAVE_FENCE();
+#pragma unroll
+      for (int s = 0; s < S; ++s) fload(lds, lds + A_STAGE, s, s);
+    }
+#else
+    if (n > 0) {
+      if (UA_ANY && kw == 0) {
+        gload_first();
+        sstore_first();
+      } else {
+        gload(kw, 0);
+        sstore(0, 0);
+      }
+      if (n > 1) gload(kw + KWAVES, 0);
+      WAVE_FENCE();
+#pragma unroll
+      for (int s = 0; s < S; ++s) fload(lds, lds + A_STAGE, s, s);
+    }
+#endif
+    // Step i, its fragments in set `set` (being read): half of its MFMAs, the
+    // reads of the next step's fragments, the other half.
+    auto body = [&](IDX_T i, auto set1) {
+      constexpr int set = decltype(set1)::value ? 1 : 0;
+      FRAG_WAIT();
+#if DIRECT_LDS
+      // the reads of stage `set` are complete: step i + 2 goes there
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      WAVE_FENCE();
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + 2 < n) dload_part(cur, kw + (i + 2) * KWAVES, set, 0, A_NL + B_NL, lego_bool<false>());
+#endif
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < S / 2; ++s) mfma_all(set * S + s);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + 1 < n) {
+        const elem_t* na = lds + (set ^ 1) * STAGE;
+#if DIRECT_LDS
+        wait_tiles(i + 2 < n ? 1 : 0);
+        __builtin_amdgcn_sched_barrier(0);
+#else
+        sstore(set ^ 1, 0);
+        if (i + 2 < n) gload(kw + (i + 2) * KWAVES, 0);
+#endif
+        WAVE_FENCE();
+#pragma unroll
+        for (int s = 0; s < S; ++s) fload(na, na + A_STAGE, s, (set ^ 1) * S + s);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = S / 2; s < S; ++s) mfma_all(set * S + s);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    IDX_T i = 0;
+    for (; i + 1 < n; i += 2) {
+      body(i, lego_bool<false>());
+      body(i + 1, lego_bool<true>());
+    }
+    if (i < n) body(i, lego_bool<false>());
+    __syncthreads();  // every wave is done with its stages
+    f4_t* red = (f4_t*)lds_all;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < NREG; r += 4) {
+          const f4_t v = {acc[i][j][r], acc[i][j][r + 1], acc[i][j][r + 2], acc[i][j][r + 3]};
+          red[(kw * (NACC / 4) + (((i * NI + j) * NREG + r) / 4)) * 64u + lane] = v;
+          acc[i][j][r] = acc[i][j][r + 1] = acc[i][j][r + 2] = acc[i][j][r + 3] = 0.0f;
+        }
+    __syncthreads();
+#if C_SEP
+    float* __restrict__ Cb = C + c_t(tm, tn);
+#endif
+#pragma unroll
+    for (int q = 0; q < GPW; ++q) {
+      const IDX_T g = kw * GPW + q;
+      f4_t v = red[g * 64u + lane];
+#pragma unroll
+      for (int k = 1; k < KWAVES; ++k) v += red[(k * (NACC / 4) + g) * 64u + lane];
+      const IDX_T blk = g / (NREG / 4), r0 = g % (NREG / 4) * 4u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+#if C_EDGE
+        if (!c_ok(tm, tn, lane, w, blk / NI, blk % NI, r0 + e)) continue;
+#endif
+#if C_SEP
+        __builtin_nontemporal_store(v[e], Cb + c_l(lane, w, blk / NI, blk % NI, r0 + e));
+#else
+        __builtin_nontemporal_store(v[e], C + c_f(tm, tn, lane, w, blk / NI, blk % NI, r0 + e));
+#endif
+      }
+    }
+    pid += gridDim.x;
+    if (pid < (IDX_T)(GEMM_MT * GEMM_NT)) __syncthreads();  // the sums have been read
+  } while (pid < (IDX_T)(GEMM_MT * GEMM_NT));
+#elif DIRECT_LDS
   const IDX_T ntiles = (IDX_T)(GEMM_MT * GEMM_NT);
   IDX_T pid = blockIdx.x;
   Tile cur = tile_of(pid);
+  set_edges(cur);
   // Every stage of the ring is filled up front; afterwards step g+NSTAGES is
   // requested as soon as the barrier of step g has retired the last reader of
   // its stage (a substep before step g+1 begins).  Every step requests one
   // step's copies (with fewer k-steps than stages, repeats of the tile's
   // steps), so the number in flight at each barrier is always the same.
 #pragma unroll
-  for (int p = 0; p < NSTAGES; ++p) dload_part(cur, (IDX_T)p % KT, p, 0, A_NV + B_NV);
+  for (int p = 0; p < NSTAGES; ++p) {
+    if (p == 0)
+      dload_part(cur, 0, 0, 0, A_NL + B_NL, lego_bool<EDGE_K>());
+    else
+      dload_part(cur, (IDX_T)p % KT, p, 0, A_NL + B_NL, lego_bool<false>());
+  }
   wait_tiles(NSTAGES - 1);
   __syncthreads();
   // Fragments are read FRAG_DIST substeps ahead of their MFMAs; the barrier
@@ -637,24 +944,25 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
           // Each row: its MFMAs with this row's share of the copies and of
           // the next fragments between them, one instruction after each MFMA.
           mfma_row(i, s % NFB);
-          if (r < R) dload_part(ct, ck, cur_stage, r * (A_NV + B_NV) / R, (r + 1) * (A_NV + B_NV) / R);
+          if (r < R) dload_part(ct, ck, cur_stage, r * (A_NL + B_NL) / R, (r + 1) * (A_NL + B_NL) / R, lego_bool<false>());
           fload_part(ra, ra + A_STAGE, ts, ts % NFB, i * (MI + NI) / MI, (i + 1) * (MI + NI) / MI);
           // after MFMA g of the row: a copy (even g) or a fragment read (odd
           // g); with FRAG_SPREAD 3 the copy's LDS address (M0) is set one
           // MFMA ahead, so no wait state separates the two
 #pragma unroll
           for (int g = 0; g < NI; ++g) {
-            if (FRAG_SPREAD >= 3 && g % 2 == 0 && g / 2 < (A_NV + B_NV) / R)
+            if (FRAG_SPREAD >= 3 && g % 2 == 0 && g / 2 < (A_NL + B_NL) / R)
               __builtin_amdgcn_sched_group_barrier(0x004, 1, 0);  // M0
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-            if (g % 2 == 0 && g / 2 < (A_NV + B_NV) / R) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            if (g % 2 == 0 && g / 2 < (A_NL + B_NL) / R) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
             if (g % 2 == 1 && g / 2 < (MI + NI) / MI) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
           }
           __builtin_amdgcn_sched_barrier(0);
 #else
           mfma_row(i, s % NFB);
           __builtin_amdgcn_sched_barrier(0);
-          if (r < R) dload_part(ct, ck, cur_stage, r * (A_NV + B_NV) / R, (r + 1) * (A_NV + B_NV) / R);
+          if (r < R)
+            dload_part(ct, ck, cur_stage, r * (A_NL + B_NL) / R, (r + 1) * (A_NL + B_NL) / R, lego_bool<false>());
           if (i == 0) fload(ra, ra + A_STAGE, ts, ts % NFB);
           __builtin_amdgcn_sched_barrier(0);
 #endif
@@ -662,7 +970,7 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
         continue;
       }
 #else
-      if (s == S - FRAG_DIST) dload_part(ct, ck, cur_stage, 0, A_NV + B_NV);
+      if (s == S - FRAG_DIST) dload_part(ct, ck, cur_stage, 0, A_NL + B_NL, lego_bool<false>());
 #endif
 #if FRAG_SPREAD >= 2
       // The next fragments go out one after each MFMA of the first rows, so
@@ -796,7 +1104,7 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
   // the first fragment reads of step t.  Stage t&1 was last read in step
   // t-2, before that step's barrier.
   constexpr int S = BK / KB;
-  constexpr int NL = A_NV + B_NV;  // load / store vectors per thread and tile
+  constexpr int NL = A_NL + B_NL;  // load / store vectors per thread and tile
   auto pipe_step = [&](IDX_T kt) {
     const int cur = kt & 1;
     const elem_t* la = lds + cur * STAGE;
@@ -819,8 +1127,10 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
       // Part s of tile kt+1 goes to LDS; part s-1, written one substep
       // earlier, is reloaded with tile kt+2 (reloading registers that an LDS
       // write still has to read would stall the wave until that write drains).
-      if (s < S - 1 && kt + 1 < KT) sstore_part(cur ^ 1, 0, s * NL / (S - 1), (s + 1) * NL / (S - 1));
-      if (s > 0 && kt + 2 < KT) gload_part(kt + 2, 0, (s - 1) * NL / (S - 1), s * NL / (S - 1));
+      if (s < S - 1 && kt + 1 < KT)
+        sstore_part(cur ^ 1, 0, s * NL / (S - 1), (s + 1) * NL / (S - 1), lego_bool<false>());
+      if (s > 0 && kt + 2 < KT)
+        gload_part(kt + 2, 0, (s - 1) * NL / (S - 1), s * NL / (S - 1), lego_bool<false>());
       // one MFMA, then one of each kind of memory instruction, while they last
 #pragma unroll
       for (int g = 0; g < MI * NI; ++g) {
@@ -832,16 +1142,16 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  gload(0, 0);
-  sstore(0, 0);
+  gload_first();
+  sstore_first();
   if (1 < KT) gload(1, 0);
   __syncthreads();
   fload(lds, lds + A_STAGE, 0, 0);
   for (IDX_T kt = 0; kt < KT; ++kt) pipe_step(kt);
 #elif PREFETCH == 2
-  gload(0, 0);
+  gload_first();
   if (1 < KT) gload(1, 1);
-  sstore(0, 0);
+  sstore_first();
   __syncthreads();
   for (IDX_T kt = 0; kt < KT; kt += 2) {
     step(kt, 0, 1);
@@ -850,8 +1160,8 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
 #else
   // Single staging set: the tile for step kt+1 is loaded at the top of step
   // kt and stored during it.
-  gload(0, 0);
-  sstore(0, 0);
+  gload_first();
+  sstore_first();
   __syncthreads();
   for (IDX_T kt = 0; kt < KT; ++kt) {
     if (kt + 1 < KT) gload(kt + 1, 0);
@@ -869,7 +1179,7 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
       mfma_all(s & 1);
       if (s == STORE_AT) {
 #pragma unroll
-        for (int g = 0; g < A_NV * (A_SVEC ? A_VR : A_V) + B_NV * (B_SVEC ? B_VR : B_V); ++g) {
+        for (int g = 0; g < A_NL * (A_SVEC ? A_VR : A_V) + B_NL * (B_SVEC ? B_VR : B_V); ++g) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
         }
@@ -879,7 +1189,7 @@ extern "C" __global__ __launch_bounds__(NT) void lego_gemm(const elem_t* __restr
     __syncthreads();
   }
 #endif
-#if !DIRECT_LDS
+#if !DIRECT_LDS && KWAVES == 1
   store_c(tm, tn);
 #endif
 }
