@@ -336,7 +336,14 @@ Sum mul(const Ctx& c, const Sum& x, const Sum& y) {
   if (y.is_const()) return mulc(c, x, y.c0);
   std::vector<Sum> k = {x, y};
   std::sort(k.begin(), k.end(), [](const Sum& a, const Sum& b) { return skey(a) < skey(b); });
-  return atom_sum(make_op(Op::Mul, k, 0, imul(range(x), range(y))));
+  Interval r = imul(range(x), range(y));
+  // x * (x + 1) and x * x are non-negative for every integer x, also where
+  // the interval of x reaches below zero (the antidiagonal formulas at points
+  // past the extents, which a masked box computes and drops): their halves
+  // then stay in 32-bit code.
+  const Sum d = sub(c, y, x);
+  if (d.t.empty() && d.c0 >= -1 && d.c0 <= 1) r.lo = std::max<i64>(r.lo, 0);
+  return atom_sum(make_op(Op::Mul, k, 0, r));
 }
 
 Sum fdiv(const Ctx& c, const Sum& x, i64 n) {

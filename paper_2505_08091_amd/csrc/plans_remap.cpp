@@ -1,5 +1,6 @@
 // Planning of index-map evaluation and layout remap kernels.
 #include <algorithm>
+#include <cmath>
 #include <functional>
 #include <map>
 #include <numeric>
@@ -208,6 +209,9 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
   // them in flight: 4096^2 fp32 antidiagonal -> Row 5.3 -> 6.1 TB/s), as do
   // 8-byte elements (LDS and registers).
   const bool beyond_llc = 2 * n[0] * n[1] * elem_bytes > (i64(256) << 20);
+  // (Narrow elements too: 128- or 256-wide boxes with several neighbouring
+  // elements a lane measured 1.1-1.9 times slower, 4659^2 fp16 antidiagonal
+  // 24.8 / 26.1 us at 64, 35.3 / 43.4 at 128.)
   const i64 B = tune("remap.box_side", beyond_llc && n[0] >= 128 && n[1] >= 128 && elem_bytes <= 4 ? 128 : 64);
   const char* names[3] = {"rows", "cols", "antidiags"};
   // Box element (a, b) of lane l on line p: row p, column p, or the pair of
@@ -288,8 +292,9 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
   // 6.66 TB/s; 4096^2: 5.33 / 5.99 -> 5.72 / 5.95), Morton order and tiles
   // of 8 or 16 boxes.
   const bool ad_lines = os == 2 || od == 2;
-  const bool xcd = nb % 8 == 0;
-  long long bt = ad_lines && nbr == nbc && nbr % 2 == 0 && xcd ? nbr / 2 : 0;
+  const bool even = nb % 8 == 0;
+  const bool xcd = nb >= 8;
+  long long bt = ad_lines && nbr == nbc && nbr % 2 == 0 && even ? nbr / 2 : 0;
   bt = tune("remap.box_tile", bt);
   const bool ad_boxes = bt > 0 && nbr % bt == 0 && nbc % bt == 0;
   const i64 per_cu = std::max<i64>(1, std::min<i64>(8, (160 * 1024) / (B * B * elem_bytes)));
@@ -301,15 +306,51 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
     Wb = make_tileorderby({make_row({nbr / bt, nbc / bt}), make_row({bt / band, 1}), make_col({band, bt})});
   else
     band = 0;
+  // Other grids: bands of `rows` box rows, column by column inside (the last
+  // band takes the rows left over), an eighth of this order per XCD: boxes that
+  // share the lines at their edges (every one, where a row's length is not a
+  // multiple of the line) meet in one L2, close in time.  An XCD's share
+  // of about nb / 8 boxes is a square up to 128 MiB of traffic (4659^2 fp16:
+  // 18.1 us, 26.3 in bands of 8 rows), bands of 8 rows beyond (5001^2 fp32
+  // 52.3, squares 53.2); bands of 4 rows where antidiagonals are read, and row
+  // by row where those come from beyond the last-level cache.  Against row-major order without XCDs, there
+  // / back: 4659^2 fp16 30.7 / 30.5 -> 18.1 / 24.0 us; 4501^2 fp32 54.7 / 49.4
+  // -> 42.4 / 39.6; 7501^2 fp32 157 / 115 -> 121 / 114 (bands of 8 read back
+  // 123, of 4 118); 6001x7001 fp32 transpose 91 / 93 -> 82 / 80.
+  i64 rows = 0;
+  if (!ad_boxes && xcd) {
+    const bool small = 2 * n[0] * n[1] * elem_bytes <= (i64(128) << 20);
+    const i64 cap = os == 2 ? (beyond_llc ? 1 : 4) : small ? nbr : 8;
+    rows = std::max<i64>(1, std::min<i64>({nbr, cap, (i64)std::llround(std::sqrt(nb / 8.0))}));
+    rows = std::min<i64>(nbr, std::max(1ll, tune("remap.box_rows", rows)));
+  }
   auto box_fn = [&](Ctx& c) {
     int b = c.var("b", nb);
     SymAlg al{&c};
     Sum pos = var(c, b);
-    if (xcd) pos = add(c, mulc(c, fmod(c, var(c, b), 8), nb / 8), fdiv(c, var(c, b), 8));
+    if (xcd) {
+      // XCD x = b % 8 has the positions from x * (nb / 8) + min(x, nb % 8) on
+      const Sum x = fmod(c, var(c, b), 8);
+      Sum first = mulc(c, x, nb / 8);
+      if (!even) first = add(c, first, select(c, lt(c, x, cst(nb % 8)), x, cst(nb % 8)));
+      pos = add(c, first, fdiv(c, var(c, b), 8));
+    }
     FnSpec f;
     f.params = {b};
-    f.outs = Wb->inv(al, pos);
     f.out_bound = {nbr, nbc};
+    if (!rows) {
+      f.outs = Wb->inv(al, pos);
+      return f;
+    }
+    const i64 left = nbr % rows, whole = nbr / rows * rows;
+    const Sum in = fmod(c, pos, rows * nbc);
+    Sum bi = add(c, mulc(c, fdiv(c, pos, rows * nbc), rows), fmod(c, in, rows)), bj = fdiv(c, in, rows);
+    if (left) {
+      const Sum rest = sub(c, pos, cst(whole * nbc)), in_whole = lt(c, pos, cst(whole * nbc));
+      bi = select(c, in_whole, bi, add(c, cst(whole), fmod(c, rest, left)));
+      bj = select(c, in_whole, bj, fdiv(c, rest, left));
+    }
+    f.outs = {bi, bj};
     return f;
   };
   // Element offset of lane l on row, column or antidiagonal r of box (bi,
@@ -412,7 +453,9 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
   R.grid = nb;
   R.src = s.str();
   R.info = "box " + std::to_string(B) + "x" + std::to_string(B) +
-           (ad_boxes ? " tiles" + std::to_string(bt) + (band ? "-bands" + std::to_string(band) : "") : " row") +
+           (ad_boxes ? " tiles" + std::to_string(bt) + (band ? "-bands" + std::to_string(band) : "")
+            : rows   ? " bands" + std::to_string(rows)
+                     : " row") +
            (xcd ? "-xcd" : "") + " load " + names[os] + (ssep ? " sep" : " full") + " (" + std::to_string(bs) +
            " runs) store " + names[od] + (dsep ? " sep" : " full") + " (" + std::to_string(bd) + " runs) pad " +
            std::to_string(pad) + (nontemporal & 1 ? " nt-loads" : "") + (nontemporal & 2 ? " nt-stores" : "") +
@@ -728,6 +771,17 @@ static RemapPlan plan_remap_impl(const Layout& src, const Layout& dst, int elem_
   }
   const int VL = pow2_vec(srun, maxv);
   const int VS = pow2_vec(drun, maxv);
+  // Extents without the factors of two that 16-byte vectors need on both
+  // sides: a 2-D map takes square boxes instead, whose lines do not depend on
+  // the extents' factors, where both sides run along some kind of line.  Row
+  // to column-major, LDS tiles -> boxes: 7236x2955 fp32 63 -> 41 us,
+  // 3003x3001 fp64 200 -> 33, 5001x7003 fp16 189 / 420 (back) -> 35, 1001x999
+  // u8 7.8 -> 3.8.  With few boxes and a tile of some KiB the tiles are
+  // the faster ones (517x207 fp64, 36 boxes: 3.4 / 3.0 against 3.7 / 3.9).
+  if ((VL * elem_bytes < 16 || VS * elem_bytes < 16) && !dst.expand_inner && tune("remap.box", 1) != 0) {
+    RemapPlan box;
+    if (plan_remap_box(src, dst, elem_bytes, &box) && (box.grid >= 64 || TILE * elem_bytes < 4096)) return box;
+  }
   // Split tile digits so that a source vector (the lowest VL of the tile's
   // source order) and a destination vector (the lowest VS of its destination
   // order) are made of whole digits.  Splitting a digit keeps the map; it

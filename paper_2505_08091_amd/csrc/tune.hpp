@@ -4,8 +4,9 @@
 // default is what the measurements chose).  Keys: gemm.lds_s, gemm.mfma,
 // gemm.direct, gemm.prefetch, gemm.rolling, gemm.dma_spread, gemm.frag_dist,
 // gemm.frag_spread, gemm.store_at, gemm.persist, gemm.ring_unroll, gemm.wide_waves, gemm.zdirect, gemm.zpair,
-// gemm.dma_rows, index.nt_store, index.grid, remap.nontemporal, remap.box,
-// remap.box_side, remap.box_tile, remap.box_band, remap.nt, remap.unroll, remap.order (0 destination, 1
+// gemm.dma_rows, gemm.ua, gemm.bm, gemm.bn, gemm.bk, gemm.wm, gemm.wn,
+// gemm.kwaves and gemm.stages (together: the default tile), index.nt_store, index.grid, remap.nontemporal, remap.box,
+// remap.box_side, remap.box_tile, remap.box_band, remap.box_rows, remap.nt, remap.unroll, remap.order (0 destination, 1
 // source), remap.xcd, remap.persist, remap.tile_bytes, remap.block (LDS block
 // transfer), remap.swizzle, remap.swizzle2, remap.lds_row (LDS XOR key strides
 // and row bytes).
