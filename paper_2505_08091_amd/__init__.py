@@ -136,16 +136,17 @@ def _current_stream():
     return _RAW_STREAM()
 
 
-def _stream(stream):
+def _raw_stream(stream):
+    """The stream's handle as an int, which ctypes passes as a void pointer."""
     if stream is None:
-        return ctypes.c_void_p(_current_stream())
+        return (_RAW_STREAM or _current_stream)()
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+def _stream(stream):
+    return ctypes.c_void_p(_raw_stream(stream))
 
 
 class _Handle:
@@ -232,10 +233,16 @@ class Layout(_Handle):
         _check(_lib.lego_orderby(self.h, len(pieces), arr, ctypes.byref(out)))
         return Layout(out)
 
+    # A layout is immutable: its rank and sizes are asked for once (every
+    # device call compares buffers with them, 0.44 us a query).
+    _rank = _size = _phys = None
+
     def rank(self):
-        r = ctypes.c_int()
-        _check(_lib.lego_layout_rank(self.h, ctypes.byref(r)))
-        return r.value
+        if self._rank is None:
+            r = ctypes.c_int()
+            _check(_lib.lego_layout_rank(self.h, ctypes.byref(r)))
+            self._rank = r.value
+        return self._rank
 
     def dims(self):
         n = self.rank()
@@ -244,15 +251,19 @@ class Layout(_Handle):
         return list(d)
 
     def size(self):
-        n = ctypes.c_int64()
-        _check(_lib.lego_layout_size(self.h, ctypes.byref(n)))
-        return n.value
+        if self._size is None:
+            n = ctypes.c_int64()
+            _check(_lib.lego_layout_size(self.h, ctypes.byref(n)))
+            self._size = n.value
+        return self._size
 
     def phys_size(self):
         """Elements of a buffer in this layout (ExpandBy: the original extents)."""
-        n = ctypes.c_int64()
-        _check(_lib.lego_layout_phys_size(self.h, ctypes.byref(n)))
-        return n.value
+        if self._phys is None:
+            n = ctypes.c_int64()
+            _check(_lib.lego_layout_phys_size(self.h, ctypes.byref(n)))
+            self._phys = n.value
+        return self._phys
 
     def apply(self, idx):
         if len(idx) != self.rank():
@@ -344,16 +355,22 @@ def mfma_fragment_layout(instr, operand):
 
 
 # ------------------------------------------------------------------ device --
+# The time of a small call is the host's (a launch alone takes about 2.5 us of
+# it), so the wrappers do no more than the checks and the call.
 def apply_all_device(layout, out, stream=None):
     """out[x] = apply(x) for every logical flat x (out: int32/int64 cuda tensor)."""
     _need(out, layout.size(), "output")
-    _check(_lib.lego_apply_all_device(layout.h, out.element_size(), _ptr(out), _stream(stream)))
+    rc = _lib.lego_apply_all_device(layout.h, out.element_size(), out.data_ptr(), _raw_stream(stream))
+    if rc:
+        _check(rc)
 
 
 def inv_all_device(layout, out, stream=None):
     """out[p, k] = inv(p)[k] for every physical p (out: [N, rank] int32/int64)."""
     _need(out, layout.phys_size() * layout.rank(), "output")
-    _check(_lib.lego_inv_all_device(layout.h, out.element_size(), _ptr(out), _stream(stream)))
+    rc = _lib.lego_inv_all_device(layout.h, out.element_size(), out.data_ptr(), _raw_stream(stream))
+    if rc:
+        _check(rc)
 
 
 def _need(t, n, what):
@@ -365,11 +382,14 @@ def _need(t, n, what):
 def remap(src_layout, dst_layout, src, dst, stream=None):
     """dst[dst.apply(x)] = src[src.apply(x)] for all logical x (cuda tensors);
     positions of dst outside an ExpandBy source's extents become zero."""
-    if src.element_size() != dst.element_size():
+    eb = src.element_size()
+    if eb != dst.element_size():
         raise LegoError(-1, "source and destination element sizes differ")
     _need(src, src_layout.phys_size(), "source")
     _need(dst, dst_layout.phys_size(), "destination")
-    _check(_lib.lego_remap(src_layout.h, dst_layout.h, src.element_size(), _ptr(src), _ptr(dst), _stream(stream)))
+    rc = _lib.lego_remap(src_layout.h, dst_layout.h, eb, src.data_ptr(), dst.data_ptr(), _raw_stream(stream))
+    if rc:
+        _check(rc)
 
 
 def remap_plan(src_layout, dst_layout, elem_bytes):
@@ -384,24 +404,25 @@ def remap_plan(src_layout, dst_layout, elem_bytes):
 
 def _desc(M, N, K, dtype, a=None, b=None, c=None, sched=None, lds_a=None, lds_b=None, bm=0, bn=0, bk=0, wm=0, wn=0,
           group_m=0, xcd_remap=1, stages=0, max_workgroups=0, frag_a=None, frag_b=None, frag_c=None):
-    d = lego_gemm_desc()
-    d.M, d.N, d.K = int(M), int(N), int(K)
-    d.in_dtype = DTYPES[dtype] if isinstance(dtype, str) else int(dtype)
-    d.bm, d.bn, d.bk, d.wm, d.wn, d.group_m, d.xcd_remap = bm, bn, bk, wm, wn, group_m, xcd_remap
-    d.stages = stages
-    d.max_workgroups = max_workgroups
-    for name, lay in (("a", a), ("b", b), ("c", c), ("sched", sched), ("lds_a", lds_a), ("lds_b", lds_b),
-                      ("frag_a", frag_a), ("frag_b", frag_b), ("frag_c", frag_c)):
-        setattr(d, name, lay.h if lay is not None else None)
-    return d
+    # (positional, in the order of the structure's fields)
+    return lego_gemm_desc(
+        int(M), int(N), int(K), DTYPES[dtype] if isinstance(dtype, str) else int(dtype), bm, bn, bk, wm, wn, group_m,
+        xcd_remap, stages, max_workgroups,
+        None if a is None else a.h, None if b is None else b.h, None if c is None else c.h,
+        None if sched is None else sched.h, None if lds_a is None else lds_a.h, None if lds_b is None else lds_b.h,
+        None if frag_a is None else frag_a.h, None if frag_b is None else frag_b.h,
+        None if frag_c is None else frag_c.h)
 
 
 def gemm(A, B, C, M, N, K, dtype, stream=None, **kw):
     """C (fp32) = A @ B with operands in their layouts (cuda tensors)."""
-    for t, lay, n, what in ((A, kw.get("a"), M * K, "A"), (B, kw.get("b"), K * N, "B"), (C, kw.get("c"), M * N, "C")):
-        _need(t, lay.phys_size() if lay is not None else n, what)
-    d = _desc(M, N, K, dtype, **kw)
-    _check(_lib.lego_gemm(ctypes.byref(d), _ptr(A), _ptr(B), _ptr(C), _stream(stream)))
+    a, b, c = kw.get("a"), kw.get("b"), kw.get("c")
+    _need(A, M * K if a is None else a.phys_size(), "A")
+    _need(B, K * N if b is None else b.phys_size(), "B")
+    _need(C, M * N if c is None else c.phys_size(), "C")
+    rc = _lib.lego_gemm(_desc(M, N, K, dtype, **kw), A.data_ptr(), B.data_ptr(), C.data_ptr(), _raw_stream(stream))
+    if rc:
+        _check(rc)
 
 
 def gemm_plan(M, N, K, dtype, **kw):

@@ -2,6 +2,7 @@
 #include "gemm_plan.hpp"
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdlib>
 #include <map>
@@ -1249,17 +1250,20 @@ GemmPlan plan_gemm(const GemmRequest& rq0) {
 }
 
 namespace {
+// The request as numbers, its layouts by address: the cache holds references,
+// so a cached layout is never freed and its address never another's.
+using PlanKey = std::array<i64, 21>;
+PlanKey plan_key(const GemmRequest& r) {
+  auto id = [](const LayoutP& l) { return (i64)(intptr_t)l.get(); };
+  return {r.M, r.N, r.K, r.dtype, r.bm, r.bn, r.bk, r.wm, r.wn, r.group_m, r.xcd, r.stages,
+          id(r.a), id(r.b), id(r.c), id(r.sched), id(r.lds_a), id(r.lds_b), id(r.frag_a), id(r.frag_b), id(r.frag_c)};
+}
 std::mutex g_mu;
-std::map<std::string, std::pair<std::vector<LayoutP>, std::shared_ptr<GemmPlan>>> g_cache;
+std::map<PlanKey, std::pair<std::vector<LayoutP>, std::shared_ptr<GemmPlan>>> g_cache;
 }  // namespace
 
 std::shared_ptr<GemmPlan> gemm_plan_cached(const GemmRequest& rq) {
-  std::ostringstream k;
-  k << rq.M << "," << rq.N << "," << rq.K << "," << rq.dtype << "," << rq.bm << "," << rq.bn << "," << rq.bk << ","
-    << rq.wm << "," << rq.wn << "," << rq.group_m << "," << rq.xcd << "," << rq.stages;
-  for (auto* l : {&rq.a, &rq.b, &rq.c, &rq.sched, &rq.lds_a, &rq.lds_b, &rq.frag_a, &rq.frag_b, &rq.frag_c})
-    k << "," << (const void*)l->get();
-  std::string key = k.str();
+  const PlanKey key = plan_key(rq);
   {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_cache.find(key);
