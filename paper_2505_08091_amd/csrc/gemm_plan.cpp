@@ -250,8 +250,13 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
       SCH = make_from_piece(make_row({Mt, Nt}));
   }
   if (!ragged_groups) need_dims(SCH, {Mt, Nt}, "schedule");
-  const bool xcd = rq.xcd && P % 8 == 0;
-  LayoutP XCD = xcd ? make_orderby(make_groupby({P / 8, 8}), {make_regp({P / 8, 8}, {2, 1})}) : nullptr;
+  // Tile counts that 8 does not divide: XCD x takes the tiles from
+  // x * (P / 8) + min(x, P % 8) on, in the same order (376x3864x7712 64.5 ->
+  // 56.6 us, 900x1100x700 10.7 -> 9.9, 3700^3 120 -> 117).  Not a few
+  // 256-wide tiles, of which no XCD has enough to share (2200x2900x1700, 108
+  // tiles: 53.7 without, 54.9 with).
+  const bool xcd = rq.xcd && (P % 8 == 0 || P >= ((i64)bm * bn < 256 * 256 ? 16 : 128));
+  LayoutP XCD = xcd && P % 8 == 0 ? make_orderby(make_groupby({P / 8, 8}), {make_regp({P / 8, 8}, {2, 1})}) : nullptr;
   LayoutP SA = rq.lds_a ? rq.lds_a : default_lds(bm, bk);
   LayoutP SB = rq.lds_b ? rq.lds_b : default_lds(bn, bk);
   need_dims(SA, {bm, bk}, "LDS A");
@@ -689,11 +694,17 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
                    SymAlg al{&c};
                    int pid = c.var("pid", P);
                    Sum q = var(c, pid);
-                   if (xcd) q = XCD->apply(al, unflatten(al, {P / 8, 8}, q));
+                   if (XCD) {
+                     q = XCD->apply(al, unflatten(al, {P / 8, 8}, q));
+                   } else if (xcd) {
+                     const Sum x = fmod(c, q, 8);
+                     q = add(c, add(c, mulc(c, x, P / 8), select(c, lt(c, x, cst(P % 8)), x, cst(P % 8))), fdiv(c, q, 8));
+                   }
                    FnSpec f;
                    f.params = {pid};
                    if (!ragged_groups) {
                      f.outs = SCH->inv(al, q);
+                     if (xcd && !XCD) f.out_bound = {Mt, Nt};
                      return f;
                    }
                    // Tile coordinates, whatever the interval of the branch not
@@ -1155,36 +1166,43 @@ namespace {
 // as rounds * k-steps * step + fixed, rounds = ceil(tiles / 256 CUs), a 64-deep
 // k-step costing `step` with few tiles and `step + full` when every CU has one
 // (L2 and power are shared), in microseconds.  Fitted to graph-replayed
-// launches of 22 shapes (fp16; in brackets the tile that is now taken and the
-// 256-wide tile that was the only default):
-//   2048^3 row/row 25.3 (128) / 41.0, 1024^3 7.4 (64) / 22.5, 512^3 3.4 (32) /
+// launches of 26 shapes (fp16; in brackets the tile that is now taken, then
+// the 256-wide tile that was the only default):
+//   2048^3 row/row 24 (128) / 41.0, 1024^3 7.4 (64) / 22.5, 512^3 3.4 (32) /
 //   14.2, 960x576x832 6.5 (64) / 18.5, 256x3712x1024 7.3 (64) / 21.8,
 //   128x8192x8192 44.4 (64) / 108, 256x256x8192 13.0 (32) / 120,
-//   1536x1536x4096 31.7 (128) / 68.5, 3999x2001x1111 36.7 (128) / 48.1;
-//   256-wide tiles stay ahead at 3000^3 (84 against 106 with 128) and
-//   1344x5696x5952 (117 against 133).
+//   1536x1536x4096 31.5 (128) / 68.5, 3999x2001x1111 36.7 (128) / 48.1,
+//   2560^3 41.6 (256x128; 128: 46) / 52.8, 1040x4464x2120 39.1 (256x128; 128:
+//   53) / 56.9; 256-wide tiles stay ahead at 3000^3 (83 against 103 with 128)
+//   and 1344x5696x5952 (114 against 120).
 // The 64- and 32-wide tiles are computed whole by each of 4 waves along K:
 // without barriers and with half the LDS reads they measured 7.4 against 7.6
 // (1024^3), 7.3 against 8.7 (256x3712x1024) and 22.3 against 28.9 us
-// (256x256x8192) of 4 waves with 32x32 of the tile each.
+// (256x256x8192) of 4 waves with 32x32 of the tile each.  128-wide tiles are
+// bound by what the L2s deliver (about 16 TB/s at 2048^3: with half the LDS
+// reads, 4 waves along K that share the stages, the time was the same).
 struct TileChoice {
-  int b, wm, wn, kwaves;
+  int bm, bn, wm, wn, kwaves;
   double step, full, fixed;
+  bool direct_only;  // register-staged copies measured slower than with 128-wide tiles
 };
 const TileChoice kTiles[] = {
-    {256, 0, 0, 0, 1.15, 0.6, 6.0},  // wave tiles by the rule of plan_gemm
-    {128, 64, 32, 0, 0.43, 0.25, 4.0},
-    {64, 64, 64, 4, 0.15, 0.13, 3.0},
-    {32, 32, 32, 4, 0.08, 0.04, 2.5},
+    {256, 256, 0, 0, 0, 1.08, 0.65, 6.0, false},  // wave tiles by the rule of plan_gemm
+    {256, 128, 64, 64, 0, 0.55, 0.4, 5.0, true},
+    {128, 256, 64, 64, 0, 0.55, 0.4, 5.0, true},
+    {128, 128, 64, 32, 0, 0.43, 0.22, 4.0, false},
+    {64, 64, 64, 64, 4, 0.15, 0.13, 3.0, false},
+    {32, 32, 32, 32, 4, 0.08, 0.04, 2.5, false},
 };
 
-const TileChoice& choose_tile(const GemmRequest& rq) {
+const TileChoice& choose_tile(const GemmRequest& rq, bool direct) {
   const TileChoice* best = nullptr;
   double best_t = 0;
   for (const TileChoice& t : kTiles) {
-    const double p = (double)((rq.M + t.b - 1) / t.b) * (double)((rq.N + t.b - 1) / t.b);
+    if (t.direct_only && !direct) continue;
+    const double p = (double)((rq.M + t.bm - 1) / t.bm) * (double)((rq.N + t.bn - 1) / t.bn);
     const double fill = std::min(1.0, p / 256), steps = (double)((rq.K + 63) / 64);
-    const double full = t.full * (t.b == 256 ? fill * fill : fill);
+    const double full = t.full * (t.wm ? fill : fill * fill);
     const double us = std::ceil(p / 256) * steps * (t.step + full) + t.fixed;
     if (!best || us < best_t) best = &t, best_t = us;
   }
@@ -1205,9 +1223,18 @@ GemmPlan plan_gemm(const GemmRequest& rq0) {
     rq.kwaves = (int)tune("gemm.kwaves", 0);
     rq.stages = (int)tune("gemm.stages", 0);
   } else if (free_tile) {
-    const TileChoice& t = choose_tile(rq);
-    if (t.b < 256) {
-      rq.bm = rq.bn = t.b;
+    const TileChoice* choice = &choose_tile(rq, true);
+    if (choice->direct_only) {
+      rq.bm = choice->bm, rq.bn = choice->bn, rq.bk = 64;
+      rq.wm = choice->wm, rq.wn = choice->wn;
+      GemmPlan p = plan_gemm_waves(rq, true);
+      if (p.direct) return p;
+      rq = rq0;
+      choice = &choose_tile(rq, false);
+    }
+    const TileChoice& t = *choice;
+    if (t.wm) {
+      rq.bm = t.bm, rq.bn = t.bn;
       rq.wm = t.wm, rq.wn = t.wn;
       rq.kwaves = t.kwaves;
       rq.bk = 64;
@@ -1225,7 +1252,7 @@ GemmPlan plan_gemm(const GemmRequest& rq0) {
         rq.bm = rq.bn = 64, rq.wm = rq.wn = 32, rq.kwaves = 0;
         return plan_gemm_waves(rq, true);
       }
-      if (t.b == 64 && (rq.K <= 1024 || !p.direct)) {
+      if (t.bm == 64 && (rq.K <= 1024 || !p.direct)) {
         try {
           rq.bk = 32;
           return plan_gemm_waves(rq, true);
