@@ -34,7 +34,13 @@ CASES = [(size, tile, la, lb) for size in SIZES for tile in TILES for la, lb in
 # grouped schedules with a ragged last group (more than 8 tile rows)
 DIRECT = [((200, 136, 72), {}), ((72, 264, 40), {}), ((264, 72, 1032), {}), ((712, 72, 136), {}),
           ((264, 136, 200), dict(bm=128, bn=128, bk=64, wm=64, wn=32)), ((1096, 256, 72), dict(bm=64, bn=64, bk=32, wm=32, wn=32)),
-          ((520, 520, 2048), dict(max_workgroups=3))]
+          ((520, 520, 2048), dict(max_workgroups=3)),
+          # 256x128 and 128x256 tiles, and tile counts that 8 does not divide
+          # in XCD order (18 and 15 * 9 tiles)
+          ((520, 264, 200), dict(bm=256, bn=128, bk=64, wm=64, wn=64)),
+          ((264, 520, 200), dict(bm=128, bn=256, bk=64, wm=64, wn=64)),
+          ((712, 328, 72), dict(bm=128, bn=128, bk=64, wm=64, wn=32)),
+          ((960, 576, 832), dict(bm=64, bn=64, bk=64, wm=32, wn=32))]
 
 HARNESS = r"""
 template <class GP, class GC, class NV, class GL, class OK>

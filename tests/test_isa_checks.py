@@ -207,7 +207,7 @@ def _gemm_case_ids():
 def _measured_gemms(L):
     """The measured GEMMs that the GPU tests do not launch at these sizes."""
     if L is None:
-        return [None] * 6
+        return [None] * 11
     n = 8192
     out = [dict(M=8000, N=8000, K=8000, dtype="bf16")]
     for la in ("Row", "Col"):
@@ -215,6 +215,10 @@ def _measured_gemms(L):
             out.append(dict(M=n, N=n, K=n, dtype="f16", a=L.as_layout(getattr(L, la)(n, n)),
                             b=L.as_layout(getattr(L, lb)(n, n))))
     out.append(dict(M=1024, N=1024, K=1024, dtype="f16", bm=128, bn=128, bk=32, wm=64, wn=64))
+    # one size of each tile that the default plans take below 256 x 256 (both
+    # 256 x 128 and 128 x 256), with transposing reads of both operands
+    for m, n, k in ((2560, 2560, 2560), (1040, 4464, 2120), (2048, 2048, 2048), (1000, 1000, 1000), (256, 256, 8192)):
+        out.append(dict(M=m, N=n, K=k, dtype="f16", a=L.as_layout(L.Col(m, k)), b=L.as_layout(L.Row(k, n))))
     return out
 
 
