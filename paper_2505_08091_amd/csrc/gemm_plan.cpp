@@ -1153,6 +1153,7 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
        << "B ops" << opsinfo.str();
   g.info = info.str();
   g.direct = direct;
+  g.wide = wide;
   g.vec8 = ops[0].V == 8 && ops[1].V == 8;
   g.wide_ok = direct && !((ops[0].frtr || ops[1].frtr) && (ops[0].edge || ops[1].edge || cedge));
   return g;
@@ -1209,6 +1210,48 @@ const TileChoice& choose_tile(const GemmRequest& rq, bool direct) {
   return *best;
 }
 
+// The plan of a request without a tile with the tile chosen for it; no plan
+// (an empty source) where that is the 256-wide one.
+GemmPlan plan_chosen_tile(const GemmRequest& rq0) {
+  GemmRequest rq = rq0;
+  const TileChoice* choice = &choose_tile(rq, true);
+  if (choice->direct_only) {
+    rq.bm = choice->bm, rq.bn = choice->bn, rq.bk = 64;
+    rq.wm = choice->wm, rq.wn = choice->wn;
+    GemmPlan p = plan_gemm_waves(rq, true);
+    if (p.direct) return p;
+    choice = &choose_tile(rq0, false);
+  }
+  const TileChoice& t = *choice;
+  if (!t.wm) return GemmPlan();
+  rq.bm = t.bm, rq.bn = t.bn;
+  rq.wm = t.wm, rq.wn = t.wn;
+  rq.kwaves = t.kwaves;
+  rq.bk = 64;
+  if (!t.kwaves) return plan_gemm_waves(rq, true);
+  // 64-wide tiles along K: 32-deep steps spread a short K over the waves
+  // more evenly (960x576x832: 6.5 against 7.2 us, 1000x777x1001 with odd
+  // rows 10.8 against 15.2; 128x8192x8192 the other way, 58.7 against
+  // 44.4), and staged loads of 64 leave too few registers.
+  // (The 16x16x32 instruction has one substep in 32, which the waves
+  // along K cannot halve.)
+  GemmPlan p = plan_gemm_waves(rq, true);
+  if (!p.vec8) {
+    // Loads narrower than 16 bytes take more registers than a wave along
+    // K has: 4 waves with 32x32 of a 64x64 tile each.
+    rq.bm = rq.bn = 64, rq.wm = rq.wn = 32, rq.kwaves = 0;
+    return plan_gemm_waves(rq, true);
+  }
+  if (t.bm == 64 && (rq.K <= 1024 || !p.direct)) {
+    try {
+      rq.bk = 32;
+      return plan_gemm_waves(rq, true);
+    } catch (const Unsupported&) {
+    }
+  }
+  return p;
+}
+
 }  // namespace
 
 GemmPlan plan_gemm(const GemmRequest& rq0) {
@@ -1223,45 +1266,13 @@ GemmPlan plan_gemm(const GemmRequest& rq0) {
     rq.kwaves = (int)tune("gemm.kwaves", 0);
     rq.stages = (int)tune("gemm.stages", 0);
   } else if (free_tile) {
-    const TileChoice* choice = &choose_tile(rq, true);
-    if (choice->direct_only) {
-      rq.bm = choice->bm, rq.bn = choice->bn, rq.bk = 64;
-      rq.wm = choice->wm, rq.wn = choice->wn;
-      GemmPlan p = plan_gemm_waves(rq, true);
-      if (p.direct) return p;
-      rq = rq0;
-      choice = &choose_tile(rq, false);
-    }
-    const TileChoice& t = *choice;
-    if (t.wm) {
-      rq.bm = t.bm, rq.bn = t.bn;
-      rq.wm = t.wm, rq.wn = t.wn;
-      rq.kwaves = t.kwaves;
-      rq.bk = 64;
-      if (!t.kwaves) return plan_gemm_waves(rq, true);
-      // 64-wide tiles along K: 32-deep steps spread a short K over the waves
-      // more evenly (960x576x832: 6.5 against 7.2 us, 1000x777x1001 with odd
-      // rows 10.8 against 15.2; 128x8192x8192 the other way, 58.7 against
-      // 44.4), and staged loads of 64 leave too few registers.
-      // (The 16x16x32 instruction has one substep in 32, which the waves
-      // along K cannot halve.)
-      GemmPlan p = plan_gemm_waves(rq, true);
-      if (!p.vec8) {
-        // Loads narrower than 16 bytes take more registers than a wave along
-        // K has: 4 waves with 32x32 of a 64x64 tile each.
-        rq.bm = rq.bn = 64, rq.wm = rq.wn = 32, rq.kwaves = 0;
-        return plan_gemm_waves(rq, true);
-      }
-      if (t.bm == 64 && (rq.K <= 1024 || !p.direct)) {
-        try {
-          rq.bk = 32;
-          return plan_gemm_waves(rq, true);
-        } catch (const Unsupported&) {
-        }
-      }
-      return p;
-    }
+    // Kernels with 64-bit indices (a reversed C at any size) keep the 256-wide
+    // default: with waves along K they abort the run-time compiler's
+    // instruction selection, and the process with it.
+    GemmPlan p = plan_chosen_tile(rq0);
+    if (!p.src.empty() && !p.wide) return p;
   }
+
   // 128x128 wave tiles (4 waves) win where the copies are direct: 0.852
   // against 0.876 ms for 8 waves of 128x64 on the 8192^3 bf16 GEMM, reading
   // 1/3 less LDS per MFMA, and 1-5% with transposing fragment reads (8192^3

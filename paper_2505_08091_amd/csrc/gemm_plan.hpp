@@ -30,6 +30,7 @@ struct GemmPlan : KernelPlan {
   bool wide_ok = false;
   bool direct = false;  // global-to-LDS copies without registers
   bool vec8 = false;    // both operands are loaded 16 bytes at a time
+  bool wide = false;    // 64-bit indices
 };
 
 GemmRequest gemm_request(const lego_gemm_desc& d, const std::function<LayoutP(lego_layout_t)>& resolve);

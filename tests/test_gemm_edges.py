@@ -151,3 +151,23 @@ def test_element_aligned_operands(lego, i):
 @pytest.mark.parametrize("i", range(len(DIRECT)))
 def test_padded_direct_copies(lego, i, la, lb):
     _check(lego, *DIRECT[i], la, lb, ("f16", "bf16")[i % 2])
+
+
+@pytest.mark.parametrize("size", [(64, 128, 192), (256, 256, 256), (65, 63, 65), (600, 1000, 72)])
+def test_reversed_c_keeps_the_wide_tiles(lego, size, tmp_path):
+    """A reversed C puts the kernel in 64-bit indices, which with waves along K
+    abort the compiler: such plans keep the tiles of the larger sizes, and
+    compile."""
+    import os
+    import subprocess
+    from tests.test_isa_checks import HIPCC
+    M, N, K = size
+    src = lego.plan_source("gemm", M=M, N=N, K=K, dtype="f16", c=lego.as_layout(lego.GenP("reverse", [M, N])))
+    assert "#define KWAVES 1\n" in src
+    if not os.path.exists(HIPCC):
+        pytest.skip("no ROCm compiler")
+    (tmp_path / "k.hip").write_text(src)
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "--genco", "-Xclang", "-target-feature",
+                        "-Xclang", "-packed-fp32-ops", "-include", "hip/hip_runtime.h", str(tmp_path / "k.hip"), "-o",
+                        str(tmp_path / "k.co")], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-2000:]
