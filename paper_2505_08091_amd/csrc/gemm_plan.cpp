@@ -158,6 +158,7 @@ struct Operand {
   bool edge = false;      // some loads fall outside the operand (padded tiles)
   bool user_lds = false;  // LDS layout given by the caller
   bool direct = false;  // load vector q fills LDS slot q (direct global-to-LDS copy)
+  bool soff = false;    // direct: the tile and k-step part of an offset may be a copy's scalar offset
   bool ua = false;      // vectors of 8 loaded at element alignment, cut at the operand's edges
 };
 
@@ -660,6 +661,13 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
       Sum off = glob_off(c, o, var(c, tt), var(c, kt), i, j);
       Sum pt, r1, pk, pl;
       o.sep = split_by(off, {tt}, &pt, &r1) && split_by(r1, {kt}, &pk, &pl);
+      // A range-checked copy adds its lane offset and its scalar offset as
+      // unsigned 32-bit numbers and checks the lane offset against what the
+      // scalar one leaves of the buffer: every part of an offset has to be
+      // non-negative by itself (an order that runs backwards along the tiles
+      // or k-steps has negative ones, which would pass the check and read
+      // 4 GiB away).  Other operands put the whole offset into the lanes' part.
+      o.soff = o.sep && range(pt).lo >= 0 && range(pk).lo >= 0 && range(pl).lo >= 0;
     }
   }
   const i64 stage_bytes = 2ll * (bm + bn) * bk;
@@ -1059,7 +1067,7 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
       << "FRZP " << (o.frzp ? 1 : 0) << "\n#define " << P2[k]
       << "NVEC " << (o.ua ? 8 * o.NVEC : o.NVEC) << "u\n#define " << P2[k]
       << "GUARD " << (o.guard ? 1 : 0) << "\n#define " << P2[k] << "EDGE " << (o.edge ? 1 : 0) << "\n#define "
-      << P2[k] << "UA " << (o.ua ? 1 : 0) << "\n#define " << P2[k] << "LOC_T "
+      << P2[k] << "SOFF " << (o.soff ? 1 : 0) << "\n#define " << P2[k] << "UA " << (o.ua ? 1 : 0) << "\n#define " << P2[k] << "LOC_T "
       << (!o.ua ? "IDX_T" : (2 * o.glob->phys_size() < (i64(1) << 31) ? "int" : "i64")) << "\n#define "
       << P2[k] << "BUF " << (o.direct && 2 * o.glob->phys_size() < (i64(1) << 31) ? 1 : 0) << "\n#define "
       << P2[k] << "BYTES " << 2 * o.glob->phys_size() << "u\n#define " << P2[k] << "VR " << o.VR << "\n#define "

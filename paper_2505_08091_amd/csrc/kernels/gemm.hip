@@ -41,6 +41,8 @@
 //   A_BUF (and B_BUF): direct copies are range-checked buffer loads with
 //       32-bit byte offsets (operands under 2 GiB; 0.5% faster than global
 //       loads on the 8192^3 bf16 GEMM, and fewer address registers)
+//   A_SOFF (and B_SOFF): a_gt + a_gk may be a buffer load's scalar offset: no
+//       part of an offset is negative by itself
 //   A_EDGE, a_ok(tm, kt, tid, u), A_BYTES (and B_*): tiles padded past the
 //       operand (Section III-D partial tiles): load vector u is inside (1) or
 //       padding (0, read as zero); the operand's size in bytes
@@ -604,8 +606,9 @@ extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __re
   const IDX_T wu = __builtin_amdgcn_readfirstlane(tid / 64u);
 #endif
 #if A_BUF || B_BUF
-  // Range-checked buffer loads: an offset past the buffer's end (0xFFFFFFFF
-  // for padding) writes zero to the LDS slot instead of reading memory.
+  // Range-checked buffer loads: an offset past the buffer's end writes zero to
+  // the LDS slot instead of reading memory.  Padding passes 0xFFFFFFFF where
+  // the lanes carry whole offsets, OUTSIDE beside a scalar one.
   const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)A, (short)0, (int)A_BYTES, 0x00020000);
   const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)B, (short)0, (int)B_BYTES, 0x00020000);
 #endif
@@ -639,19 +642,19 @@ extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __re
   // the 64-wide plans of waves along K, none now.)
   constexpr bool EDGE_K = (A_EDGE || B_EDGE) && GEMM_K % BK != 0;
   constexpr unsigned OUTSIDE = 0x80000000u;
-#if A_EDGE && A_SEP
+#if A_EDGE && A_SOFF
   unsigned a_vo[A_NL];
 #endif
-#if B_EDGE && B_SEP
+#if B_EDGE && B_SOFF
   unsigned b_vo[B_NL];
 #endif
   auto set_edges = [&](const Tile& t) {
     (void)t;
-#if A_EDGE && A_SEP
+#if A_EDGE && A_SOFF
 #pragma unroll
     for (int u = 0; u < A_NL; ++u) a_vo[u] = a_ok(t.tm, 0, tid, u) ? (unsigned)a_loc[u] * 2u : OUTSIDE;
 #endif
-#if B_EDGE && B_SEP
+#if B_EDGE && B_SOFF
 #pragma unroll
     for (int u = 0; u < B_NL; ++u) b_vo[u] = b_ok(t.tn, 0, tid, u) ? (unsigned)b_loc[u] * 2u : OUTSIDE;
 #endif
@@ -674,7 +677,7 @@ extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __re
 #endif
       __attribute__((address_space(3))) void* dst = (__attribute__((address_space(3))) void*)(la + ((IDX_T)u * NT + wu * 64u) * 8u);
 #if A_BUF
-#if A_EDGE && A_SEP
+#if A_EDGE && A_SOFF
       (void)src;
       const unsigned soff = (unsigned)((t.ab - A) + a_gk(kt)) * 2u;
       const unsigned off = !first ? a_vo[u] : a_ok(t.tm, kt, tid, u) ? (unsigned)a_loc[u] * 2u : OUTSIDE;
@@ -682,7 +685,7 @@ extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __re
 #elif A_EDGE
       const unsigned off = a_ok(t.tm, kt, tid, u) ? (unsigned)((src - A) * 2) : 0xFFFFFFFFu;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, dst, 16, off, 0, 0, 0);
-#elif A_SEP
+#elif A_SOFF
       // The lane's byte offset is fixed; the tile and k-step part is one
       // scalar offset, so a copy costs no vector arithmetic.
       (void)src;
@@ -705,7 +708,7 @@ extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __re
 #endif
       __attribute__((address_space(3))) void* dst = (__attribute__((address_space(3))) void*)(lb + ((IDX_T)u * NT + wu * 64u) * 8u);
 #if B_BUF
-#if B_EDGE && B_SEP
+#if B_EDGE && B_SOFF
       (void)src;
       const unsigned soff = (unsigned)((t.bb - B) + b_gk(kt)) * 2u;
       const unsigned off = !first ? b_vo[u] : b_ok(t.tn, kt, tid, u) ? (unsigned)b_loc[u] * 2u : OUTSIDE;
@@ -713,7 +716,7 @@ extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __re
 #elif B_EDGE
       const unsigned off = b_ok(t.tn, kt, tid, u) ? (unsigned)((src - B) * 2) : 0xFFFFFFFFu;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, off, 0, 0, 0);
-#elif B_SEP
+#elif B_SOFF
       (void)src;
       const unsigned soff = (unsigned)((t.bb - B) + b_gk(kt)) * 2u;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, dst, 16, b_loc[u] * 2u, soff, 0, 0);
