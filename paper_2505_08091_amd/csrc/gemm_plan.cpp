@@ -716,9 +716,7 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
                      return f;
                    }
                    // Tile coordinates, whatever the interval of the branch not
-                   // taken: the range keeps the whole kernel in 32-bit indices
-                   // (64-bit ones also abort the compiler's instruction
-                   // selection on some padded-tile kernels).
+                   // taken: the range keeps the whole kernel in 32-bit indices.
                    f.out_bound = {Mt, Nt};
                    // Full groups first, then the ragged group of r = Mt % G rows.
                    const i64 full = Mt / G * G, r = Mt % G, nfull = full * Nt;
@@ -1068,7 +1066,7 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
       << "NVEC " << (o.ua ? 8 * o.NVEC : o.NVEC) << "u\n#define " << P2[k]
       << "GUARD " << (o.guard ? 1 : 0) << "\n#define " << P2[k] << "EDGE " << (o.edge ? 1 : 0) << "\n#define "
       << P2[k] << "SOFF " << (o.soff ? 1 : 0) << "\n#define " << P2[k] << "UA " << (o.ua ? 1 : 0) << "\n#define " << P2[k] << "LOC_T "
-      << (!o.ua ? "IDX_T" : (2 * o.glob->phys_size() < (i64(1) << 31) ? "int" : "i64")) << "\n#define "
+      << (o.soff ? "u32" : !o.ua ? "IDX_T" : (2 * o.glob->phys_size() < (i64(1) << 31) ? "int" : "i64")) << "\n#define "
       << P2[k] << "BUF " << (o.direct && 2 * o.glob->phys_size() < (i64(1) << 31) ? 1 : 0) << "\n#define "
       << P2[k] << "BYTES " << 2 * o.glob->phys_size() << "u\n#define " << P2[k] << "VR " << o.VR << "\n#define "
       << P2[k] << "VC " << (o.axis == 2 ? o.VC : o.ua ? 1 : o.V) << "\n";
@@ -1275,8 +1273,8 @@ GemmPlan plan_gemm(const GemmRequest& rq0) {
     rq.stages = (int)tune("gemm.stages", 0);
   } else if (free_tile) {
     // Kernels with 64-bit indices (a reversed C at any size) keep the 256-wide
-    // default: with waves along K they abort the run-time compiler's
-    // instruction selection, and the process with it.
+    // default: the model of kTiles is of 32-bit kernels, and with waves along K
+    // those of odd rows spill (777x1000x1001, reversed C: 70 registers).
     GemmPlan p = plan_chosen_tile(rq0);
     if (!p.src.empty() && !p.wide) return p;
   }

@@ -54,8 +54,12 @@
 //       tile's first k-step with vectors past the operand's rows moved onto
 //       it, and, for the last k-step, a_gc(tm, tid, u) the offset moved back
 //       until all 8 elements lie inside the operand and a_nv(tm, tid, u) how
-//       many of the vector's elements exist (0..8); A_LOC_T is a signed type
-//       that holds offsets inside a tile
+//       many of the vector's elements exist (0..8)
+//   A_LOC_T (and B_LOC_T): the type of the lanes' offsets inside a tile, signed
+//       with A_UA; with A_SOFF the 32 bits that a buffer load takes, also in
+//       kernels with 64-bit indices (64-bit ones cut to 32 bits at each copy
+//       end the compiler in a floating-point exception while it selects
+//       instructions: 188 of 720 tried kernels with a reversed C)
 //   KWAVES           > 1: each of KWAVES waves computes the whole workgroup tile
 //                    over every KWAVES-th k-step in LDS stages of its own (the
 //                    generated functions describe one wave, NT = 64), and the

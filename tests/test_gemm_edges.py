@@ -155,9 +155,8 @@ def test_padded_direct_copies(lego, i, la, lb):
 
 @pytest.mark.parametrize("size", [(64, 128, 192), (256, 256, 256), (65, 63, 65), (600, 1000, 72)])
 def test_reversed_c_keeps_the_wide_tiles(lego, size, tmp_path):
-    """A reversed C puts the kernel in 64-bit indices, which with waves along K
-    abort the compiler: such plans keep the tiles of the larger sizes, and
-    compile."""
+    """A reversed C puts the kernel in 64-bit indices: such plans keep the tiles
+    of the larger sizes, and compile."""
     import os
     import subprocess
     from tests.test_isa_checks import HIPCC

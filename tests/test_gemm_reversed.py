@@ -1,4 +1,4 @@
-"""GEMM operands in orders that run backwards along tiles or k-steps.
+"""GEMMs whose operands or result run backwards along tiles or k-steps.
 
 A range-checked direct copy adds a scalar offset (tile and k-step) and a lane
 offset as unsigned 32-bit numbers; the hardware checks the lane's against what
@@ -6,6 +6,8 @@ the scalar one leaves of the buffer.  An order that runs backwards has negative
 parts, which must not become scalar offsets: every copy is replayed on the host
 with the kernel's 32-bit arithmetic.  On the GPU the products are compared with
 the fp64 oracle: products are exact in fp32 and the sums have at most 512 terms.
+Negative parts also put a kernel in 64-bit indices, of which some forms end the
+compiler; the code-object checks compile these configurations (COMPILED).
 """
 import tempfile
 
@@ -26,13 +28,15 @@ EXPRS = {"rows": ("(n0-1-i)*n1+j", ["n0-1-x/n1", "x%n1"]),
          "columns": ("(n1-1-j)*n0+i", ["x%n0", "n1-1-x/n0"]),
          "vectors of a row": ("i*n1+(n1/8-1-j/8)*8+j%8", ["x/n1", "(n1/8-1-(x%n1)/8)*8+x%8"]),
          "vectors of a column": ("j*n0+(n0/8-1-i/8)*8+i%8", ["(n0/8-1-(x%n0)/8)*8+x%8", "x/n0"])}
-ORDERS = ["Row", "Col", *EXPRS, "tiles"]
+ORDERS = ["Row", "Col", *EXPRS, "tiles"]  # and "all": every element backwards (C)
 
 
 def _layouts(L, order, m, n):
     """The library's layout and the oracle's."""
     if order in EXPRS:
         return L.as_layout(L.GenPExpr([m, n], *EXPRS[order])), OL.as_layout(GX.expr_genp([m, n], *EXPRS[order]))
+    if order == "all":
+        return L.as_layout(L.GenP("reverse", [m, n])), OL.as_layout(OL.reverse_genp(m, n))
     if order == "tiles":
         return (L.TileOrderBy(L.GenP("reverse", [m // 64, n // 64]), L.Row(64, 64)),
                 OL.TileOrderBy(OL.reverse_genp(m // 64, n // 64), OL.Row(64, 64)))
@@ -107,23 +111,38 @@ def test_copies_stay_inside_the_operands(lego, size):
     assert direct >= 20
 
 
-# operands and tiles of the products on the GPU
-PRODUCTS = [((256, 256, 256), "rows", "columns", TILE), ((256, 256, 512), "columns", "rows", {}),
-            ((320, 192, 128), "tiles", "vectors of a row", TILE), ((320, 192, 128), "rows", "vectors of a column", TILE),
-            ((200, 136, 72), "vectors of a column", "rows", {}), ((520, 264, 200), "columns", "vectors of a column", TILE),
-            ((520, 264, 200), "vectors of a row", "rows", TILE)]
+# orders of A, B and C and the tile of the products on the GPU
+PRODUCTS = [((256, 256, 256), "rows", "columns", "Row", TILE), ((256, 256, 512), "columns", "rows", "Row", {}),
+            ((320, 192, 128), "tiles", "vectors of a row", "Row", TILE),
+            ((320, 192, 128), "rows", "vectors of a column", "Row", TILE),
+            ((200, 136, 72), "vectors of a column", "rows", "Row", {}),
+            ((520, 264, 200), "columns", "vectors of a column", "Row", TILE),
+            ((520, 264, 200), "vectors of a row", "rows", "Row", TILE),
+            # one operand or C alone
+            ((256, 256, 256), "rows", "Col", "Row", TILE), ((320, 192, 128), "Row", "tiles", "Row", TILE),
+            ((640, 64, 64), "Row", "Col", "all", {}), ((168, 768, 384), "Col", "Row", "all", {}),
+            ((256, 384, 320), "Row", "Col", "rows", TILE), ((200, 136, 72), "Col", "Row", "columns", {})]
+# compiled only: sizes at which the compiler ended
+COMPILED = [((1024, 1024, 1024), "Row", "Col", "rows", {}), ((512, 1024, 1088), "Col", "Row", "rows", {}),
+            ((1024, 1024, 384), "Row", "Col", "rows", TILE), ((2560, 2560, 320), "Row", "rows", "Row", {}),
+            ((2560, 2560, 320), "vectors of a row", "Col", "Row", {})]
 
 
-def _case(lego, size, a, b, tile):
+def _case(lego, size, a, b, c, tile):
+    """Keyword arguments of the call, and the oracle's layouts of A, B and C."""
     M, N, K = size
-    (la, oa), (lb, ob) = _layouts(lego, a, M, K), _layouts(lego, b, K, N)
-    return dict(a=la, b=lb, **tile), oa, ob
+    (la, oa), (lb, ob), (lc, oc) = (_layouts(lego, o, m, n) for o, m, n in ((a, M, K), (b, K, N), (c, M, N)))
+    return dict(a=la, b=lb, c=lc, **tile), oa, ob, oc
+
+
+def compiled_cases(lego):
+    return [dict(zip("MNK", case[0]), dtype="f16", **_case(lego, *case)[0]) for case in PRODUCTS + COMPILED]
 
 
 @pytest.mark.parametrize("i", range(len(PRODUCTS)))
 def test_product_sources_on_host(lego, i):
     M, N, K = PRODUCTS[i][0]
-    kw, _, _ = _case(lego, *PRODUCTS[i])
+    kw = _case(lego, *PRODUCTS[i])[0]
     src = lego.plan_source("gemm", M=M, N=N, K=K, dtype="f16", **kw)
     with tempfile.TemporaryDirectory() as tmp:
         assert _compile_and_run(src, HARNESS, tmp).strip() == "ok"
@@ -136,7 +155,7 @@ def test_products(lego, i):
     import torch
     dev = need_gpu()
     M, N, K = PRODUCTS[i][0]
-    kw, oa, ob = _case(lego, *PRODUCTS[i])
+    kw, oa, ob, oc = _case(lego, *PRODUCTS[i])
     dtype = ("f16", "bf16")[i % 2]
     say(f"gemm reversed {PRODUCTS[i]} {dtype} plan={lego.gemm_plan(M, N, K, dtype, **kw)}")
     a = S.tensor(M * K, dtype, dist="normal", seed=S.SEED_A)
@@ -149,7 +168,7 @@ def test_products(lego, i):
     lego.gemm(d_a, d_b, c, M, N, K, dtype, **kw)
     torch.cuda.synchronize()
     r = OG.gemm(a_bits, b_bits, oa, ob, dtype)
-    got = c.cpu().numpy().reshape(M, N)
+    got = OR.remap(oc, OL.as_layout(OL.Row(M, N)), c.cpu().numpy()).reshape(M, N)
     assert np.isfinite(got).all()
     ok, mre, fre = OG.check_tolerance(got, r)
     # fp32 sums of at most 512 exact products: 2-norm error below 512 * 2^-24

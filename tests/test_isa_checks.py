@@ -200,8 +200,9 @@ BUNDLER = "/opt/rocm/llvm/bin/clang-offload-bundler"
 
 
 def _gemm_case_ids():
+    from tests import test_gemm_reversed as R
     from tests.test_generated_host import N_GEMM_CASES
-    return range(N_GEMM_CASES + len(_measured_gemms(None)))
+    return range(N_GEMM_CASES + len(_measured_gemms(None)) + len(R.PRODUCTS + R.COMPILED))
 
 
 def _measured_gemms(L):
@@ -230,8 +231,9 @@ def test_gemm_configurations_compile_clean(i, tmp_path):
     if not (os.path.exists(HIPCC) and os.path.exists(BUNDLER) and os.path.exists(OBJDUMP)):
         pytest.skip("no ROCm compiler")
     import paper_2505_08091_amd as L
+    from tests import test_gemm_reversed as R
     from tests.test_generated_host import _gemm_cases
-    cases = _gemm_cases() + _measured_gemms(L)
+    cases = _gemm_cases() + _measured_gemms(L) + R.compiled_cases(L)
     kw = dict(cases[i])
     src = L.plan_source("gemm", **kw)
     hip, co, elf = tmp_path / "k.hip", tmp_path / "k.co", tmp_path / "k.elf"
