@@ -187,6 +187,11 @@ RemapPlan plan_remap(const Layout& src, const Layout& dst, int elem_bytes) {
   }
 }
 
+// A box's side, and the contiguous runs that a box has on each side of a remap.
+struct BoxLines {
+  i64 side = 0, src_runs = 0, dst_runs = 0;
+};
+
 // Box-staged remap for 2-D maps without digit structure (an element gather
 // otherwise; e.g. Row <-> antidiagonal order).  A 64 x 64 box of the logical
 // index space goes through LDS.  Each side is copied line by line, a line
@@ -199,7 +204,8 @@ RemapPlan plan_remap(const Layout& src, const Layout& dst, int elem_bytes) {
 // is the line's, and the antidiagonal order of Figure 7 is then the line's
 // start plus the row.  Returns false when no kind of line gives runs of 8
 // elements on average on both sides.
-static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes, RemapPlan* out) {
+static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes, RemapPlan* out,
+                           BoxLines* lines = nullptr) {
   const std::vector<i64> n = src.dims();
   if (n.size() != 2) return false;
   if (n[0] < 64 || n[1] < 64) return false;
@@ -247,6 +253,7 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
     if (bd < 0 || y < bd) bd = y, od = k;
   }
   if (bs * 8 > B * B || bd * 8 > B * B) return false;
+  if (lines) *lines = {B, bs, bd};
   // LDS slot of box element (a, b): a * (B + pad) + b, with the pad that
   // keeps the lanes of a wave on distinct 4-byte banks under both kinds of
   // line where it can (rows: stride 1; columns: B + pad; antidiagonals:
@@ -463,6 +470,35 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
            std::to_string(pad) + (nontemporal & 1 ? " nt-loads" : "") + (nontemporal & 2 ? " nt-stores" : "") +
            " NT=" + std::to_string(NT) + info;
   return true;
+}
+
+// Whether LDS tiles of `tile_bytes` stay ahead of boxes for a 2-D map of n
+// elements that both take; the tiles' shorter contiguous run in global memory
+// is `tile_run` bytes, copied at least `vec` bytes at a time.  A box moves one
+// element a lane, and a line that the layout breaks (tiles narrower than a
+// box) goes out in pieces.  From 937 maps that both take (us, tiles / boxes):
+//  - beyond the last-level cache broken lines cost more than short tile runs
+//    do, down to runs of about 100 bytes (row to u8 12x20 tiles, 15000^2: runs
+//    of 500 bytes 76 / 180, of 120 203 / 278, of 28 308 / 295; fp16 14x14
+//    tiles, 10300^2: to 70 / 143, back 92 / 127).  Whole lines win there but
+//    for wide runs of elements from 4 bytes on (7298x7300 fp32 transpose 84 /
+//    97; loaded 4 bytes at a time, 9125^2: 193 / 160);
+//  - inside it the pieces of a few narrow elements do, stored ones above all
+//    (row to u8 9x24 tiles, 5000^2: 8.4 / 23.3; runs of 60 bytes 14.7 / 17.1,
+//    of 36 26 / 10; fp16, 3300^2: runs of 600 bytes 8.5 / 12.7, of 200 8.6 /
+//    5.8; u8 16x8 tiles to rows 8.1 / 12.0, runs of 60 bytes 27 / 14);
+//  - a few MiB are a matter of latency, where boxes stay ahead (u8 1200^2 7.0 /
+//    3.8), and so do they of large tiles copied 1 or 2 bytes at a time (u8
+//    30x9 tiles, 42 KB: 1280 / 250).
+static bool tiles_beat_boxes(const BoxLines& lines, int elem_bytes, i64 n, i64 tile_bytes, i64 vec, i64 tile_run) {
+  const i64 runs = std::max(lines.src_runs, lines.dst_runs), bytes = 2 * n * elem_bytes;
+  const bool stores = lines.dst_runs >= lines.src_runs;  // the shorter pieces are stored
+  if (bytes < (i64(8) << 20) || (vec < 4 && tile_bytes >= 16 * 1024)) return false;
+  if (bytes > (i64(256) << 20))
+    return runs > lines.side ? tile_run >= (stores ? 100 : 128) : elem_bytes >= 4 && vec >= 8 && tile_run >= 256;
+  if (elem_bytes > 2) return false;
+  const i64 piece = elem_bytes * lines.side * lines.side / runs, e2 = elem_bytes * elem_bytes;
+  return stores ? piece < 24 && tile_run >= 60 * e2 : piece < 10 * elem_bytes && tile_run >= 150 * e2;
 }
 
 static RemapPlan plan_remap_impl(const Layout& src, const Layout& dst, int elem_bytes, bool allow_lds) {
@@ -782,7 +818,11 @@ static RemapPlan plan_remap_impl(const Layout& src, const Layout& dst, int elem_
   // the faster ones (517x207 fp64, 36 boxes: 3.4 / 3.0 against 3.7 / 3.9).
   if ((VL * elem_bytes < 16 || VS * elem_bytes < 16) && !dst.expand_inner && tune("remap.box", 1) != 0) {
     RemapPlan box;
-    if (plan_remap_box(src, dst, elem_bytes, &box) && (box.grid >= 64 || TILE * elem_bytes < 4096)) return box;
+    BoxLines lines;
+    if (plan_remap_box(src, dst, elem_bytes, &box, &lines) && (box.grid >= 64 || TILE * elem_bytes < 4096) &&
+        !tiles_beat_boxes(lines, elem_bytes, N, TILE * elem_bytes, std::min(VL, VS) * elem_bytes,
+                          std::min(srun, drun) * elem_bytes))
+      return box;
   }
   // Split tile digits so that a source vector (the lowest VL of the tile's
   // source order) and a destination vector (the lowest VS of its destination

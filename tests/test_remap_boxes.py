@@ -61,3 +61,60 @@ def test_box_remaps(lego, i):
         lego.remap(a, b, d_src, d_dst)
         torch.cuda.synchronize()
         assert (bits(d_dst.cpu()) == OR.remap(oa, ob, bits(src))).all(), CASES[i]
+
+
+# Maps that LDS tiles and boxes both take, on both sides of the rule that
+# chooses: (rows, columns, tile rows, tile columns (0: a transpose), tile order,
+# order inside a tile, element bytes, path there, path back)
+ROUTES = [(2097, 2088, 9, 24, "Row", "Col", 1, "lds", "lds"), (1197, 1176, 9, 24, "Row", "Col", 1, "box", "box"),
+          (2100, 2100, 10, 10, "Row", "Row", 1, "lds", "lds"), (3300, 3300, 10, 6, "Row", "Col", 2, "lds", "lds"),
+          (1500, 1490, 10, 10, "Col", "Row", 4, "box", "box"), (2100, 2100, 0, 0, "", "", 1, "box", "box"),
+          (15000, 15000, 12, 20, "Row", "Row", 1, "lds", "lds"), (15001, 15001, 0, 0, "", "", 1, "box", "box"),
+          (7298, 7300, 0, 0, "", "", 4, "lds", "lds"), (9125, 9125, 0, 0, "", "", 4, "box", "box"),
+          (10290, 10290, 14, 14, "Row", "Col", 2, "lds", "lds")]
+
+
+def _route_layouts(L, case):
+    m, n, t, u, outer, inner = case[:6]
+    if not t:
+        return L.as_layout(L.Row(m, n)), L.as_layout(L.Col(m, n))
+    return L.as_layout(L.Row(m, n)), L.TileOrderBy(getattr(L, outer)(m // t, n // u), getattr(L, inner)(t, u))
+
+
+def test_tiles_or_boxes(lego):
+    for case in ROUTES:
+        row, other = _route_layouts(lego, case)
+        got = tuple(lego.remap_plan(a, b, case[6])["path"] for a, b in ((row, other), (other, row)))
+        assert got == case[7:], (case, got)
+
+
+@pytest.mark.parametrize("i", [i for i in range(len(ROUTES)) if ROUTES[i][0] < 5000])
+def test_tile_and_box_sources_on_host(lego, i):
+    row, other = _route_layouts(lego, ROUTES[i])
+    orow, oother = _route_layouts(OL, ROUTES[i])
+    m, n = ROUTES[i][:2]
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "out.bin")
+        for a, b, oa, ob in ((row, other, orow, oother), (other, row, oother, orow)):
+            _compile_and_run(lego.plan_source("remap", a, b, param=ROUTES[i][6]), HARNESS_REMAP, tmp, [out])
+            perm = np.fromfile(out, dtype=np.int64)
+            assert (perm == OR.remap(oa, ob, np.arange(m * n, dtype=np.int64))).all(), ROUTES[i]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("i", [i for i in range(len(ROUTES)) if ROUTES[i][0] < 5000])
+def test_tiles_and_boxes(lego, i):
+    import torch
+    dev = need_gpu()
+    row, other = _route_layouts(lego, ROUTES[i])
+    orow, oother = _route_layouts(OL, ROUTES[i])
+    m, n, elem = ROUTES[i][0], ROUTES[i][1], ROUTES[i][6]
+    src = torch.from_numpy(np.random.default_rng(i).integers(0, 256, m * n * elem, dtype=np.uint8))
+    src = src.view({1: torch.uint8, 2: torch.int16, 4: torch.int32}[elem])
+    d_src = src.to(dev)
+    for a, b, oa, ob in ((row, other, orow, oother), (other, row, oother, orow)):
+        say(f"remap {ROUTES[i]} plan={lego.remap_plan(a, b, elem)['info']}")
+        d_dst = torch.full_like(d_src, -1 if elem > 1 else 255)
+        lego.remap(a, b, d_src, d_dst)
+        torch.cuda.synchronize()
+        assert (bits(d_dst.cpu()) == OR.remap(oa, ob, bits(src))).all(), ROUTES[i]
