@@ -324,11 +324,15 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
   // / back: 4659^2 fp16 30.7 / 30.5 -> 18.1 / 24.0 us; 4501^2 fp32 54.7 / 49.4
   // -> 42.4 / 39.6; 7501^2 fp32 157 / 115 -> 121 / 114 (bands of 8 read back
   // 123, of 4 118); 6001x7001 fp32 transpose 91 / 93 -> 82 / 80.
-  // (Transposes whose grid 8 divides keep row-major order up to 128 MiB, an
-  // eighth per XCD: 3001x1999 fp16 6.12 us, 6.17 in bands.)
+  // (Transposes of fewer than 512 boxes keep row-major order, an eighth per XCD,
+  // with its shorter index code: bands are level there or, by the launch, a
+  // little slower, 140 sizes 1.00 on average, at most 3.4 -> 3.8 us.  From
+  // 1500 boxes on bands are ahead, 46 sizes of grids that 8 divides by 4 to 5%
+  // on average for each element size: 3521x15530 u8 30.8 -> 20.8, 1988x7983
+  // fp16 13.3 -> 11.6, 2250x5592 fp32 18.4 -> 15.8, 5376x1401 fp16 6.3.)
   const bool small = 2 * n[0] * n[1] * elem_bytes <= (i64(128) << 20);
   i64 rows = 0;
-  if (!ad_boxes && xcd && !(even && !ad_lines && small)) {
+  if (!ad_boxes && xcd && (ad_lines || nb >= 512)) {
     const i64 cap = os == 2 ? (beyond_llc ? 1 : 4) : small ? nbr : 8;
     rows = std::max<i64>(1, std::min<i64>({nbr, cap, (i64)std::llround(std::sqrt(nb / 8.0))}));
     rows = std::min<i64>(nbr, std::max(1ll, tune("remap.box_rows", rows)));
