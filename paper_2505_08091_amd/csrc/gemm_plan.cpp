@@ -826,8 +826,9 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
     if (o.ua) {
       // Coordinates of load vector u of thread tid at tile tt and k-step kt
       // (an expression), and the offset of its first element with the
-      // coordinates limited to the operand: along the vector to `back`
-      // elements before the extent's end, across it to the last row.
+      // coordinates limited to the operand: across the vector to the last row
+      // (or k); along it, in the last k-step (`strict`) to 8 elements before
+      // the extent's end, in the others only where it begins past the end.
       auto at = [&, k](Ctx& c, const Sum& kt, int* tt, int* tid, int* u, Sum* row, Sum* kk) {
         const Operand& oo = ops[k];
         *tt = c.var(oo.is_b ? "tn" : "tm", oo.is_b ? Nt : Mt);

@@ -932,14 +932,13 @@ extern "C" __global__ __launch_bounds__(BLOCK) void lego_gemm(const elem_t* __re
     for (int s = 0; s < S; ++s) {
       FRAG_WAIT_NEXT();
       if (s == S - FRAG_DIST) {
-        // Every read of stage `cur_stage` has been issued and has completed
-        // (the barrier waits for this wave's LDS reads).  Once the next step's
-        // copies have landed (those requested after it may stay in flight)
-        // and all waves are here, the stage is free for step g+NSTAGES and
-        // the fragments of step g+1 can be read.
+        // Every read of stage `cur_stage` has been issued.  Once these have
+        // completed, the next step's copies have landed (those requested after
+        // it may stay in flight) and all waves are here, the stage is free for
+        // step g+NSTAGES and the fragments of step g+1 can be read.
         wait_tiles(NSTAGES - 2);
         // This wave's reads of the stage must be complete before any wave
-        // copies into it (the barrier alone does not wait for LDS reads).
+        // copies into it: the barrier itself waits for no memory operation.
         __builtin_amdgcn_s_waitcnt(0xC07F);
         BARE_BARRIER();
         __builtin_amdgcn_sched_barrier(0);
