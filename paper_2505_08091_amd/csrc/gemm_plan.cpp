@@ -45,6 +45,7 @@ GemmRequest gemm_request(const lego_gemm_desc& d, const std::function<LayoutP(le
   r.group_m = d.group_m;
   r.xcd = d.xcd_remap;
   r.stages = d.stages;
+  r.max_workgroups = d.max_workgroups;
   r.a = resolve(d.a);
   r.b = resolve(d.b);
   r.c = resolve(d.c);
@@ -1171,9 +1172,12 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
 namespace {
 
 // A workgroup tile of the default plans.  The time of a GEMM with it is taken
-// as rounds * k-steps * step + fixed, rounds = ceil(tiles / 256 CUs), a 64-deep
-// k-step costing `step` with few tiles and `step + full` when every CU has one
-// (L2 and power are shared), in microseconds.  Fitted to graph-replayed
+// as rounds * k-steps * step + (rounds - 1) * round + fixed, rounds =
+// ceil(tiles / 256 CUs, or the launch's limit of workgroups where that is
+// less), a 64-deep k-step costing `step` with few tiles and `step + full` when
+// every CU has one (L2 and power are shared), and each round after the first
+// `round` for the C stores and the first copies that the k-steps do not cover,
+// in microseconds.  step, full and fixed are fitted to graph-replayed
 // launches of 26 shapes (fp16; in brackets the tile that is now taken, then
 // the 256-wide tile that was the only default):
 //   2048^3 row/row 24 (128) / 41.0, 1024^3 7.4 (64) / 22.5, 512^3 3.4 (32) /
@@ -1189,29 +1193,43 @@ namespace {
 // (256x256x8192) of 4 waves with 32x32 of the tile each.  128-wide tiles are
 // bound by what the L2s deliver (about 16 TB/s at 2048^3: with half the LDS
 // reads, 4 waves along K that share the stages, the time was the same).
+// The 256x128 tiles are taken for one round only: with more they lose to
+// 256-wide tiles on one side of K and to 128-wide ones on the other
+// (10240x6912x944 194 against 172 with 256, 2816x7424x256 26.5 against 23.0
+// with 128).  `round` is fitted to 177 shapes with every tile (times with the
+// chosen tile, and the one taken without `round`): 4096x4096x64 14.3 (256) /
+// 16.9 (128), 4096x4096x128 16.3 (256) / 21.5 (256x128), 6144x6144x512 61 (256
+// or 128) / 78 (256x128), 4096x2048x64 8.2 to 9.5 / 9.9 (64), 8024x7736x16 94
+// (128) / 132 (256x128).  Over all of them the time is within 1.7% of the best tile's
+// on average, and twice more than 5% above the 256-wide tile's (9216x1024x8
+// 11.6 against 10.7, 12288x2048x192 30.0 against 27.3).
 struct TileChoice {
   int bm, bn, wm, wn, kwaves;
-  double step, full, fixed;
+  double step, full, fixed, round;
   bool direct_only;  // register-staged copies measured slower than with 128-wide tiles
+  bool one_round;
 };
 const TileChoice kTiles[] = {
-    {256, 256, 0, 0, 0, 1.08, 0.65, 6.0, false},  // wave tiles by the rule of plan_gemm
-    {256, 128, 64, 64, 0, 0.55, 0.4, 5.0, true},
-    {128, 256, 64, 64, 0, 0.55, 0.4, 5.0, true},
-    {128, 128, 64, 32, 0, 0.43, 0.22, 4.0, false},
-    {64, 64, 64, 64, 4, 0.15, 0.13, 3.0, false},
-    {32, 32, 32, 32, 4, 0.08, 0.04, 2.5, false},
+    {256, 256, 0, 0, 0, 1.08, 0.65, 6.0, 4.0, false, false},  // wave tiles by the rule of plan_gemm
+    {256, 128, 64, 64, 0, 0.55, 0.4, 5.0, 0, true, true},
+    {128, 256, 64, 64, 0, 0.55, 0.4, 5.0, 0, true, true},
+    {128, 128, 64, 32, 0, 0.43, 0.22, 4.0, 0.65, false, false},
+    {64, 64, 64, 64, 4, 0.15, 0.13, 3.0, 0.6, false, false},
+    {32, 32, 32, 32, 4, 0.08, 0.04, 2.5, 0.6, false, false},
 };
 
 const TileChoice& choose_tile(const GemmRequest& rq, bool direct) {
   const TileChoice* best = nullptr;
   double best_t = 0;
+  const double wgs = rq.max_workgroups > 0 ? std::min(256, rq.max_workgroups) : 256;
   for (const TileChoice& t : kTiles) {
     if (t.direct_only && !direct) continue;
     const double p = (double)((rq.M + t.bm - 1) / t.bm) * (double)((rq.N + t.bn - 1) / t.bn);
-    const double fill = std::min(1.0, p / 256), steps = (double)((rq.K + 63) / 64);
+    const double rounds = std::ceil(p / wgs);
+    if (t.one_round && rounds > 1) continue;
+    const double fill = std::min(wgs, p) / 256, steps = (double)((rq.K + 63) / 64);
     const double full = t.full * (t.wm ? fill : fill * fill);
-    const double us = std::ceil(p / 256) * steps * (t.step + full) + t.fixed;
+    const double us = rounds * steps * (t.step + full) + (rounds - 1) * t.round + t.fixed;
     if (!best || us < best_t) best = &t, best_t = us;
   }
   return *best;
@@ -1297,11 +1315,11 @@ GemmPlan plan_gemm(const GemmRequest& rq0) {
 namespace {
 // The request as numbers, its layouts by address: the cache holds references,
 // so a cached layout is never freed and its address never another's.
-using PlanKey = std::array<i64, 21>;
+using PlanKey = std::array<i64, 22>;
 PlanKey plan_key(const GemmRequest& r) {
   auto id = [](const LayoutP& l) { return (i64)(intptr_t)l.get(); };
   return {r.M, r.N, r.K, r.dtype, r.bm, r.bn, r.bk, r.wm, r.wn, r.group_m, r.xcd, r.stages,
-          id(r.a), id(r.b), id(r.c), id(r.sched), id(r.lds_a), id(r.lds_b), id(r.frag_a), id(r.frag_b), id(r.frag_c)};
+          r.max_workgroups, id(r.a), id(r.b), id(r.c), id(r.sched), id(r.lds_a), id(r.lds_b), id(r.frag_a), id(r.frag_b), id(r.frag_c)};
 }
 std::mutex g_mu;
 std::map<PlanKey, std::pair<std::vector<LayoutP>, std::shared_ptr<GemmPlan>>> g_cache;

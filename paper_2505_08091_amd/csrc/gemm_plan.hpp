@@ -19,6 +19,7 @@ struct GemmRequest {
   int dtype = LEGO_BF16;
   int bm = 0, bn = 0, bk = 0, wm = 0, wn = 0, group_m = 0, xcd = 0;
   int stages = 0;  // LDS stages; 0: chosen
+  int max_workgroups = 0;  // of the launch (<= 0: no limit); the default tile depends on it
   int kwaves = 0;  // chosen by the planner: waves that share a workgroup tile along K (<= 1: none)
   LayoutP a, b, c, sched, lds_a, lds_b;  // null: defaults
   LayoutP frag_a, frag_b, frag_c;        // null: chosen; else they select the MFMA instruction

@@ -170,3 +170,18 @@ def test_reversed_c_keeps_the_wide_tiles(lego, size, tmp_path):
                         "-Xclang", "-packed-fp32-ops", "-include", "hip/hip_runtime.h", str(tmp_path / "k.hip"), "-o",
                         str(tmp_path / "k.co")], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stderr[-2000:]
+
+
+# The default tile and the launch: (size, limit of workgroups, tile)
+CHOICES = [((4096, 4096, 64), 0, "256x256x64"), ((6144, 6144, 512), 0, "256x256x64"), ((2816, 7424, 256), 0, "128x128x64"),
+           ((2560, 2560, 2560), 0, "256x128x64"), ((8192, 8192, 8192), 0, "256x256x64"),
+           # a limit makes the rounds of smaller tiles more
+           ((1024, 4096, 64), 0, "128x128x64"), ((1024, 4096, 64), 64, "256x256x64"),
+           ((2048, 2048, 2048), 0, "128x128x64"), ((2048, 2048, 2048), 64, "256x256x64"),
+           ((512, 512, 512), 0, "32x32x64"), ((512, 512, 512), 256, "32x32x64")]
+
+
+def test_default_tile_counts_the_rounds(lego):
+    for (M, N, K), limit, tile in CHOICES:
+        plan = lego.gemm_plan(M, N, K, "f16", max_workgroups=limit)
+        assert f" tile {tile} " in plan, ((M, N, K), limit, plan)
