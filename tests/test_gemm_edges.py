@@ -40,7 +40,11 @@ DIRECT = [((200, 136, 72), {}), ((72, 264, 40), {}), ((264, 72, 1032), {}), ((71
           ((520, 264, 200), dict(bm=256, bn=128, bk=64, wm=64, wn=64)),
           ((264, 520, 200), dict(bm=128, bn=256, bk=64, wm=64, wn=64)),
           ((712, 328, 72), dict(bm=128, bn=128, bk=64, wm=64, wn=32)),
-          ((960, 576, 832), dict(bm=64, bn=64, bk=64, wm=32, wn=32))]
+          ((960, 576, 832), dict(bm=64, bn=64, bk=64, wm=32, wn=32)),
+          # waves along K, several tiles a workgroup, each tile begun with its cut
+          # last k-step: 2, 4 and 7 k-steps for the 4 waves
+          ((96, 88, 72), dict(max_workgroups=3)), ((72, 72, 200), dict(max_workgroups=3)),
+          ((136, 200, 200), dict(max_workgroups=7))]
 
 HARNESS = r"""
 template <class GP, class GC, class NV, class GL, class OK>
@@ -124,7 +128,8 @@ def _check(lego, size, tile, la, lb, dtype):
     dev = need_gpu()
     kw = _kw(lego, size, tile, la, lb, dtype)
     M, N, K, _ = (kw.pop(k) for k in ("M", "N", "K", "dtype"))
-    say(f"gemm edges {size} {tile} A {la} B {lb} {dtype} plan={lego.gemm_plan(M, N, K, dtype, **kw)}")
+    plan = lego.gemm_plan(M, N, K, dtype, **kw)
+    say(f"gemm edges {size} {tile} A {la} B {lb} {dtype} plan={plan}")
     a = S.tensor(M * K, dtype, dist="normal", seed=S.SEED_A)
     b = S.tensor(K * N, dtype, dist="normal", seed=S.SEED_B)
     c = torch.full((M * N,), float("nan"), dtype=torch.float32, device=dev)
@@ -137,6 +142,7 @@ def _check(lego, size, tile, la, lb, dtype):
     ok, mre, fre = OG.check_tolerance(got, r)
     # fp32 sums of at most 2049 exact products: 2-norm error below 2049 * 2^-24
     assert ok and fre < 2049 * 2.0 ** -24, (mre, fre)
+    return plan
 
 
 @pytest.mark.gpu
@@ -150,7 +156,26 @@ def test_element_aligned_operands(lego, i):
 @pytest.mark.parametrize("la,lb", [("Row", "Col"), ("Col", "Row")])
 @pytest.mark.parametrize("i", range(len(DIRECT)))
 def test_padded_direct_copies(lego, i, la, lb):
-    _check(lego, *DIRECT[i], la, lb, ("f16", "bf16")[i % 2])
+    plan = _check(lego, *DIRECT[i], la, lb, ("f16", "bf16")[i % 2])
+    assert " direct-lds " in plan, plan
+    # waves along K, which walk padded tiles too, where the planner chose a
+    # tile for these sizes, but not under a limit of 3 workgroups at 520 x 520
+    along_k = "bm" not in DIRECT[i][1] and DIRECT[i][0] != (520, 520, 2048)
+    assert ("x4k wave" in plan) == along_k, plan
+    assert " persistent " in plan or not along_k, plan
+
+
+def compiled_cases(lego):
+    """The configurations that run on the GPU, for the code-object checks."""
+    out = [_kw(lego, size, TILES[tile], la, lb, ("f16", "bf16")[i % 2])
+           for i, (size, tile, la, lb) in list(enumerate(CASES))[::3]]
+    for i, (size, tile) in enumerate(DIRECT):
+        for la, lb in (("Row", "Col"), ("Col", "Row")):
+            out.append(_kw(lego, size, tile, la, lb, ("f16", "bf16")[i % 2]))
+    return out
+
+
+N_COMPILED = len(CASES[::3]) + 2 * len(DIRECT)
 
 
 @pytest.mark.parametrize("size", [(64, 128, 192), (256, 256, 256), (65, 63, 65), (600, 1000, 72)])

@@ -706,11 +706,11 @@ def _gemm_cases():
     sw = L.as_layout(L.GenPExpr([256, 64], GE.SWIZZLE64_APPLY, GE.SWIZZLE64_INV))
     cases.append(dict(M=1024, N=1024, K=1024, dtype="bf16", lds_a=sw, lds_b=sw))
     from tests.test_gpu_gemm import _persistent_cases
-    cases += [{k: v for k, v in c.items() if k not in ("oa", "ob", "max_workgroups")} for c in _persistent_cases(L)]
+    cases += [{k: v for k, v in c.items() if k not in ("oa", "ob")} for c in _persistent_cases(L)]
     from tests.test_gpu_gemm import _morton_direct_cases, _morton_direct_kw
-    cases += [{k: v for k, v in _morton_direct_kw(L, c).items() if k != "max_workgroups"} for c in _morton_direct_cases(L)]
+    cases += [_morton_direct_kw(L, c) for c in _morton_direct_cases(L)]
     from tests.test_gpu_gemm import _random_cases
-    cases += [{k: v for k, v in c.items() if k not in ("oa", "ob", "max_workgroups")} for c in _random_cases(L)]
+    cases += [{k: v for k, v in c.items() if k not in ("oa", "ob")} for c in _random_cases(L)]
     M, N, K = 32768, 256, 32768  # a 2 GiB operand
     cases.append(dict(M=M, N=N, K=K, dtype="bf16", a=L.as_layout(L.Row(M, K)), b=L.as_layout(L.Col(K, N))))
     cases.append(dict(M=M, N=N, K=K, dtype="bf16", a=L.as_layout(L.Col(M, K)), b=L.as_layout(L.Row(K, N))))

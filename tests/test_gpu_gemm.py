@@ -262,7 +262,7 @@ def test_gemm_morton_a_direct(lego, i):
     omz = OL.as_layout(OL.morton_genp(M, K))
     a_mz_bits = OR.remap(OL.as_layout(OL.Row(M, K)), omz, S.as_numpy_bits(a_log))
     a_mz = torch.from_numpy(a_mz_bits.view(np.int16).copy()).view(a_log.dtype)
-    plan = lego.gemm_plan(M, N, K, dt, **{k: v for k, v in kw.items() if k != "max_workgroups"})
+    plan = lego.gemm_plan(M, N, K, dt, **kw)
     say(f"gemm Morton-A direct {case} plan={plan}")
     assert f" {case['mode']} " in plan and "direct-lds" in plan, plan
     c = _run(lego, a_mz, b, M, N, K, dt, **kw).reshape(M, N)
@@ -492,7 +492,7 @@ def test_gemm_random_configs(lego, i):
     import torch
     a = torch.from_numpy(a_bits.view(np.int16).copy()).view(a_log.dtype)
     b = torch.from_numpy(b_bits.view(np.int16).copy()).view(b_log.dtype)
-    say(f"gemm random {i}: {M}x{N}x{K} {dtype} plan={lego.gemm_plan(M, N, K, dtype, **{k: v for k, v in kw.items() if k != 'max_workgroups'})}")
+    say(f"gemm random {i}: {M}x{N}x{K} {dtype} plan={lego.gemm_plan(M, N, K, dtype, **kw)}")
     c = _run(lego, a, b, M, N, K, dtype, **kw).reshape(M, N)
     assert np.isfinite(c).all()
     r = OG.gemm(a_bits, b_bits, oa, ob, dtype)
@@ -555,9 +555,52 @@ def _persistent_cases(L):
     ]
 
 
+N_RING_CASES = 9
+
+
+def _ring_cases(L):
+    """Tile walks whose LDS ring chains from one tile into the next, in rings
+    of 2, 3 and 4 stages: k-step counts that the stage count does not divide
+    (the ring's first stage moves on from tile to tile), uneven tile counts per
+    workgroup, transposing fragment reads, Morton A, and a single workgroup
+    doing everything (plans with partial tiles do not walk)."""
+    def case(M, N, K, dtype, bm, bn, wm, wn, stages, wgs, la="Row", lb="Col"):
+        oa = OL.morton_genp(M, K) if la == "morton" else getattr(OL, la)(M, K)
+        a = L.GenP("morton", [M, K]) if la == "morton" else getattr(L, la)(M, K)
+        return dict(M=M, N=N, K=K, dtype=dtype, bm=bm, bn=bn, bk=64, wm=wm, wn=wn, a=L.as_layout(a),
+                    b=L.as_layout(getattr(L, lb)(K, N)), oa=OL.as_layout(oa), ob=OL.as_layout(getattr(OL, lb)(K, N)),
+                    max_workgroups=wgs, stages_want=stages)
+    return [
+        case(1024, 512, 1024, "bf16", 256, 256, 128, 128, 2, 3),
+        case(1024, 768, 320, "f16", 256, 256, 128, 128, 2, 5),
+        case(1024, 512, 1024, "f16", 256, 256, 128, 128, 2, 3, "Col", "Row"),
+        case(1024, 512, 512, "bf16", 256, 256, 128, 128, 2, 1),
+        case(1024, 1024, 512, "f16", 256, 256, 128, 64, 2, 5, "morton", "Row"),
+        case(1024, 768, 320, "bf16", 256, 128, 64, 64, 3, 5),
+        case(768, 1024, 448, "f16", 128, 256, 64, 64, 3, 4, "Col", "Row"),
+        case(768, 640, 384, "f16", 128, 128, 64, 32, 4, 7),
+        case(512, 640, 320, "bf16", 128, 128, 64, 32, 4, 3, "Col", "Row"),
+    ]
+
+
+@pytest.mark.parametrize("i", range(N_RING_CASES))
+def test_gemm_ring_tile_walk(lego, i):
+    kw = dict(_ring_cases(lego)[i])
+    stages = kw.pop("stages_want")
+    plan = lego.gemm_plan(kw["M"], kw["N"], kw["K"], kw["dtype"],
+                          **{k: kw[k] for k in ("a", "b", "bm", "bn", "bk", "wm", "wn")})
+    assert " persistent " in plan and " direct-lds " in plan and f" stages {stages} " in plan, plan
+    assert "k wave" not in plan, plan
+    _walk(lego, kw)
+
+
 @pytest.mark.parametrize("i", range(5))
 def test_gemm_persistent_tile_walk(lego, i):
-    kw = dict(_persistent_cases(lego)[i])
+    plan = _walk(lego, dict(_persistent_cases(lego)[i]))
+    assert "persistent" in plan and "k wave" not in plan, plan
+
+
+def _walk(lego, kw):
     M, N, K, dtype = kw.pop("M"), kw.pop("N"), kw.pop("K"), kw.pop("dtype")
     oa = kw.pop("oa", OL.as_layout(OL.Row(M, K)))
     ob = kw.pop("ob", OL.as_layout(OL.Col(K, N)))
@@ -565,9 +608,9 @@ def test_gemm_persistent_tile_walk(lego, i):
     b = S.tensor(K * N, dtype, dist="normal", seed=S.SEED_B)
     plan = lego.gemm_plan(M, N, K, dtype, **kw)
     say(f"gemm persistent {M}x{N}x{K} {dtype} {kw.get('max_workgroups')} workgroups plan={plan}")
-    assert "persistent" in plan
     c = _run(lego, a, b, M, N, K, dtype, **kw).reshape(M, N)
     assert np.isfinite(c).all()
     r = OG.gemm(S.as_numpy_bits(a), S.as_numpy_bits(b), oa, ob, dtype)
     ok, mre, fre = OG.check_tolerance(c, r)
     assert ok, (mre, fre)
+    return plan

@@ -200,9 +200,11 @@ BUNDLER = "/opt/rocm/llvm/bin/clang-offload-bundler"
 
 
 def _gemm_case_ids():
+    from tests import test_gemm_edges as E
     from tests import test_gemm_reversed as R
     from tests.test_generated_host import N_GEMM_CASES
-    return range(N_GEMM_CASES + len(_measured_gemms(None)) + len(R.PRODUCTS + R.COMPILED))
+    from tests.test_gpu_gemm import N_RING_CASES
+    return range(N_GEMM_CASES + len(_measured_gemms(None)) + len(R.PRODUCTS + R.COMPILED) + E.N_COMPILED + N_RING_CASES)
 
 
 def _measured_gemms(L):
@@ -231,9 +233,12 @@ def test_gemm_configurations_compile_clean(i, tmp_path):
     if not (os.path.exists(HIPCC) and os.path.exists(BUNDLER) and os.path.exists(OBJDUMP)):
         pytest.skip("no ROCm compiler")
     import paper_2505_08091_amd as L
+    from tests import test_gemm_edges as E
     from tests import test_gemm_reversed as R
     from tests.test_generated_host import _gemm_cases
-    cases = _gemm_cases() + _measured_gemms(L) + R.compiled_cases(L)
+    from tests.test_gpu_gemm import _ring_cases
+    cases = _gemm_cases() + _measured_gemms(L) + R.compiled_cases(L) + E.compiled_cases(L)
+    cases += [{k: v for k, v in c.items() if k not in ("oa", "ob", "stages_want")} for c in _ring_cases(L)]
     kw = dict(cases[i])
     src = L.plan_source("gemm", **kw)
     hip, co, elf = tmp_path / "k.hip", tmp_path / "k.co", tmp_path / "k.elf"
