@@ -300,7 +300,13 @@ static bool plan_remap_box(const Layout& src, const Layout& dst, int elem_bytes,
   // of 8 or 16 boxes.
   const bool ad_lines = os == 2 || od == 2;
   const bool even = nb % 8 == 0;
-  const bool xcd = nb >= 8;
+  // Antidiagonals read from more than twice the last-level cache keep the plain
+  // row-major order of boxes where 8 does not divide the grid (us, an eighth per
+  // XCD / plain): 9001^2 fp32 152 / 145, 14001^2 fp16 228 / 218, 7000^2 fp64 147 /
+  // 142, 6300^2 fp64 (635 MB of traffic) 125 / 117, but 6200^2 fp64 (615 MB) 107
+  // / 110 and 8300^2 fp32 (551 MB) 105 / 117.
+  const bool far = os == 2 && !even && 2 * n[0] * n[1] * elem_bytes > (i64(600) << 20);
+  const bool xcd = nb >= 8 && !far;
   long long bt = ad_lines && nbr == nbc && nbr % 2 == 0 && even ? nbr / 2 : 0;
   bt = tune("remap.box_tile", bt);
   const bool ad_boxes = bt > 0 && nbr % bt == 0 && nbc % bt == 0;

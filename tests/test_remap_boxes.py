@@ -88,6 +88,13 @@ def test_tiles_or_boxes(lego):
         assert got == case[7:], (case, got)
 
 
+@pytest.mark.parametrize("n,elem,order", [(6200, 8, "bands1-xcd"), (6300, 8, "row"), (8300, 4, "bands1-xcd"),
+                                          (9001, 4, "row"), (9000, 4, "row"), (12345, 2, "bands1-xcd"), (14001, 2, "row")])
+def test_order_of_boxes_reading_far_antidiagonals(lego, n, elem, order):
+    plan = lego.remap_plan(lego.as_layout(lego.GenP("antidiag", [n, n])), lego.as_layout(lego.Row(n, n)), elem)
+    assert plan["path"] == "box" and plan["info"].split()[2] == order, plan["info"]
+
+
 @pytest.mark.parametrize("i", [i for i in range(len(ROUTES)) if ROUTES[i][0] < 5000])
 def test_tile_and_box_sources_on_host(lego, i):
     row, other = _route_layouts(lego, ROUTES[i])
