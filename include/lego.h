@@ -246,8 +246,9 @@ enum { LEGO_F32 = 0, LEGO_F16 = 1, LEGO_BF16 = 2 };
 typedef struct {
   int64_t M, N, K;
   int in_dtype;          /* LEGO_F16 or LEGO_BF16 */
-  int bm, bn, bk;        /* workgroup tile; 0 = default 256x256x64 */
-  int wm, wn;            /* wave tile; 0 = default (bm/2, bn/2) */
+  int bm, bn, bk;        /* workgroup tile; all of bm..wn 0 = chosen by the sizes, 32x32x64 to
+                            256x256x64; one alone 0 = 64, 128 or 256 by M (bm) or N (bn), 64 or 32 (bk) */
+  int wm, wn;            /* wave tile; 0 = (bm/2, bn/2), bn/4 along n where a 256-wide tile needs 8 waves */
   int group_m;           /* grouping of the default schedule; 0 = 8 */
   int xcd_remap;         /* 1 = keep consecutive scheduled tiles on one XCD */
   int stages;            /* LDS stages of the k loop (2..4, within 160 KiB of LDS);

@@ -668,7 +668,9 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
       // non-negative by itself (an order that runs backwards along the tiles
       // or k-steps has negative ones, which would pass the check and read
       // 4 GiB away).  Other operands put the whole offset into the lanes' part.
-      o.soff = o.sep && range(pt).lo >= 0 && range(pk).lo >= 0 && range(pl).lo >= 0;
+      // (Operands of 2 GiB and more are copied through 64-bit addresses.)
+      o.soff = o.sep && 2 * o.glob->phys_size() < (i64(1) << 31) && range(pt).lo >= 0 && range(pk).lo >= 0 &&
+               range(pl).lo >= 0;
     }
   }
   const i64 stage_bytes = 2ll * (bm + bn) * bk;

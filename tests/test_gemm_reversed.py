@@ -111,6 +111,17 @@ def test_copies_stay_inside_the_operands(lego, size):
     assert direct >= 20
 
 
+def test_lane_offsets_of_large_operands(lego):
+    """Operands of 2 GiB and more are copied through addresses: their lane
+    offsets keep the kernel's index type, 64 bits where a tile spans 2^32
+    elements; 32-bit ones stay with the range-checked copies."""
+    for K, loc in ((1 << 20, "u32"), (1 << 25, "IDX_T")):
+        src = lego.plan_source("gemm", M=512, N=256, K=K, dtype="f16")
+        assert f"#define A_SOFF {int(loc == 'u32')}\n" in src and f"#define A_LOC_T {loc}\n" in src
+        assert f"#define A_BUF {int(loc == 'u32')}\n" in src
+        assert ("#define IDX_T i64\n" in src) == (loc == "IDX_T")
+
+
 # orders of A, B and C and the tile of the products on the GPU
 PRODUCTS = [((256, 256, 256), "rows", "columns", "Row", TILE), ((256, 256, 512), "columns", "rows", "Row", {}),
             ((320, 192, 128), "tiles", "vectors of a row", "Row", TILE),
