@@ -254,10 +254,10 @@ GemmPlan plan_gemm_waves(const GemmRequest& rq0, bool wide_waves) {
   if (!ragged_groups) need_dims(SCH, {Mt, Nt}, "schedule");
   // Tile counts that 8 does not divide: XCD x takes the tiles from
   // x * (P / 8) + min(x, P % 8) on, in the same order (376x3864x7712 64.5 ->
-  // 56.6 us, 900x1100x700 10.7 -> 9.9, 3700^3 120 -> 117).  Not a few
-  // 256-wide tiles, of which no XCD has enough to share (2200x2900x1700, 108
-  // tiles: 53.7 without, 54.9 with).
-  const bool xcd = rq.xcd && (P % 8 == 0 || P >= ((i64)bm * bn < 256 * 256 ? 16 : 128));
+  // 56.6 us, 900x1100x700 10.7 -> 9.9, 3700^3 120 -> 117; 30 shapes of 16 to
+  // 127 tiles of 256x256 at most 2% slower, 504x3840x1696 37.0 -> 32.1, 0.8%
+  // faster on average).  Not fewer than two tiles for each XCD.
+  const bool xcd = rq.xcd && (P % 8 == 0 || P >= 16);
   LayoutP XCD = xcd && P % 8 == 0 ? make_orderby(make_groupby({P / 8, 8}), {make_regp({P / 8, 8}, {2, 1})}) : nullptr;
   LayoutP SA = rq.lds_a ? rq.lds_a : default_lds(bm, bk);
   LayoutP SB = rq.lds_b ? rq.lds_b : default_lds(bn, bk);
